@@ -455,21 +455,21 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const 
 // workgroups): the first n_dkdv workgroups take key tiles, the rest query
 // tiles, so the query tiles fill the CUs that the key tiles' tail leaves idle
 // and no kernel boundary separates them.  Each part keeps its own XCD-aware,
-// heaviest-first order (tile_item; exact when n_dkdv is a multiple of the XCD
-// count).  Early keys are seen by the most queries and late queries see the
+// heaviest-first order (tile_item: n_dkdv is a multiple of its head groups, so
+// the dQ part's groups are the dK/dV part's).  Early keys are seen by the most queries and late queries see the
 // most keys: both parts run their heaviest tiles first.
 template <int D, int NK, int BMK, int NQ, int RQ, int BNQ, bool VLDS>
-__global__ __launch_bounds__(256, 2) void bwd_grad_kernel(BwdParams p, int n_dkdv, int n_ktiles, int n_qtiles) {
+__global__ __launch_bounds__(256, 2) void bwd_grad_kernel(BwdParams p, int n_dkdv, int n_qtiles) {
   static_assert(NK == 4 && NQ == 4, "four-wave workgroups");
   constexpr int B1 = DkdvLds<D, NK, BMK, 1, VLDS>::BYTES, B2 = DqLds<D, NQ, BNQ>::BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char lds[B1 > B2 ? B1 : B2];
   const int id = blockIdx.x;
-  int bh, r, split;
+  int bh, r;
   if (id < n_dkdv) {
-    tile_item(id, n_dkdv, p.BH, n_ktiles, 1, bh, r, split);
+    tile_item(id, p.BH, bh, r);
     dkdv_body<D, NK, BMK, 1, VLDS>(p, bh, r, lds);
   } else {
-    tile_item(id - n_dkdv, (int)gridDim.x - n_dkdv, p.BH, n_qtiles, 1, bh, r, split);
+    tile_item(id - n_dkdv, p.BH, bh, r);
     dq_body<D, NQ, RQ, BNQ>(p, bh, n_qtiles - 1 - r, lds);
   }
 }
@@ -505,7 +505,7 @@ static hipError_t launch_bwd_d(const BwdParams& p, hipStream_t stream) {
   const int nkt = (p.T + 32 * NK - 1) / (32 * NK);
   const int nqt = (p.T + 32 * RQ * NQ - 1) / (32 * RQ * NQ);
   hipLaunchKernelGGL((bwd_grad_kernel<D, NK, BMK, NQ, RQ, BNQ, BwdCfg<D>::VLDS_DKV>), dim3(nkt * p.BH + nqt * p.BH),
-                     dim3(256), 0, stream, p, nkt * p.BH, nkt, nqt);
+                     dim3(256), 0, stream, p, nkt * p.BH, nqt);
   return hipGetLastError();
 }
 

@@ -153,8 +153,11 @@ __global__ __launch_bounds__(64 * NW, (8 / NW) > 0 ? (8 / NW) : 1) void attn_fwd
   if constexpr (CACHED) {
     cached_item(blockIdx.x, gridDim.x, p.n_qtiles, NS, p.n_whole, bh, qt, split, nst);
   } else {
-    fwd_item(blockIdx.x, gridDim.x, p.BH, p.n_qtiles, NS, bh, qt, split);
-    nst = NS;
+    int rank;
+    tile_item(blockIdx.x, p.BH, bh, rank);
+    qt = p.n_qtiles - 1 - rank;  // later query tiles see more keys
+    split = 0;
+    nst = 1;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rw = wave % NWR, kg = wave / NWR;  // row wave, key group

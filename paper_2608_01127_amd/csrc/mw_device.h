@@ -372,47 +372,35 @@ __device__ __forceinline__ float sum_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// XCD-aware order: consecutive workgroup ids are dealt round-robin to the 8
-// XCDs; remap so that each XCD receives one contiguous range of logical work
-// items (whole heads, heaviest query tiles first), which keeps a head's K/V in
-// one XCD's L2.
+// XCD-aware order of the cached grids: consecutive workgroup ids are dealt
+// round-robin to the 8 XCDs; remap so that each XCD receives one contiguous
+// range of logical work items (whole heads, heaviest query tiles first), which
+// keeps a head's K/V in one XCD's L2.
 __device__ __forceinline__ int xcd_remap(int bid, int n) {
   if (n % 8) return bid;
   return (bid % 8) * (n / 8) + bid / 8;
 }
 
-// Work item (batch*head, query tile, key split) of forward workgroup `bid` in a
-// grid of n = BH * nqt * NS.  Later query tiles see more keys, so they go
-// first.  When BH is a multiple of 8, each XCD (workgroup ids are dealt to
-// the 8 XCDs round-robin) takes BH / 8 whole heads, and within them the query
-// tiles run heaviest first across those heads: interleaving the heads evens
-// out the XCD's finish (a simulation of the D = 64 training shape's dispatch
-// gives a 23% shorter makespan than taking the heads one after another, each
-// heaviest first).  Otherwise the XCD-aware order of xcd_remap, heads one
-// after another.
-// The same order for any tiling: workgroup `bid` of n = BH * ntiles * NS gets
-// (batch*head, tile rank, split), rank 0 being the heaviest tile of its head.
-__device__ __forceinline__ void tile_item(int bid, int n, int BH, int ntiles, int NS, int& bh, int& rank,
-                                          int& split) {
-  if (BH % 8 == 0) {
-    const int x = bid % 8, local = bid / 8, hpx = BH / 8;
-    const int r = local / (hpx * NS), rem = local - r * (hpx * NS);
-    bh = x * hpx + rem / NS;
-    rank = r;
-    split = rem % NS;
-  } else {
-    const int logical = xcd_remap(bid, n);
-    split = logical % NS;
-    bh = (logical / NS) / ntiles;
-    rank = (logical / NS) % ntiles;
-  }
+// Work order of the training grids.  Workgroup `bid` of n = BH * ntiles gets
+// (batch*head, tile rank), rank 0 being the heaviest tile of its head.
+// Workgroup ids are dealt to the 8 XCDs round-robin.  With g the largest power
+// of two up to 8 that divides BH, the XCDs x with the same x mod g share BH / g
+// whole heads, so that a head's K/V stay in 8 / g L2s, and take their tiles
+// heaviest first across those heads.  (n mod 8 is a multiple of g, so the last,
+// partial row of workgroup ids gives every group the same number.)
+// Against taking the heads one after another, whose last heads' heavy tiles
+// start late: 12 heads x 19200 tokens (D = 128, g = 4) forward 1226 -> 1048 us
+// and backward 4063 -> 3620, 15 heads x 2999 (D = 72, g = 1) backward 121 -> 104;
+// at g = 8 a simulation of the D = 64 training shape's dispatch gives a 23%
+// shorter makespan.
+__device__ __forceinline__ void tile_item(int bid, int BH, int& bh, int& rank) {
+  const int low = BH & -BH, g = low < 8 ? low : 8;  // 1, 2, 4 or 8
+  const int x = bid & 7, group = x & (g - 1), hpg = BH / g;
+  const int j = (bid >> 3) * (8 / g) + x / g;  // the group's j-th workgroup
+  rank = j / hpg;
+  bh = group * hpg + (j - rank * hpg);
 }
 
-__device__ __forceinline__ void fwd_item(int bid, int n, int BH, int nqt, int NS, int& bh, int& qt, int& split) {
-  int rank;
-  tile_item(bid, n, BH, nqt, NS, bh, rank, split);
-  qt = nqt - 1 - rank;
-}
 // Cached attention: the heads one after another on each XCD (xcd_remap).
 // Within a head, first its n_whole heaviest query tiles, unsplit (nst = 1),
 // heaviest first; then the remaining tiles over NS key ranges (nst = NS),
