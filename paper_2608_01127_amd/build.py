@@ -36,6 +36,8 @@ UNITS = [  # (object name, source, extra flags)
     ("attn_fwd128", "attn_fwd.hip", ["-DMW_FWD_HEAD_DIM=128", *ILP]),
     # the 256-row cached configuration: 64-byte loop alignment measured faster
     ("attn_fwd128c", "attn_fwd.hip", ["-DMW_FWD_HEAD_DIM=128", "-DMW_FWD_CACHED", *ILP, "-falign-loops=64"]),
+    # the tiles for grids that do not fill the card
+    ("attn_fwd128s", "attn_fwd.hip", ["-DMW_FWD_HEAD_DIM=128", "-DMW_FWD_SMALL"]),
     ("attn_fwd128dec", "attn_fwd.hip", ["-DMW_FWD_HEAD_DIM=128", "-DMW_FWD_DECODE"]),
     ("attn_bwd64", "attn_bwd.hip", ["-DMW_BWD_HEAD_DIM=64"]),
     ("attn_bwd72", "attn_bwd.hip", ["-DMW_BWD_HEAD_DIM=72"]),

@@ -464,12 +464,12 @@ __global__ __launch_bounds__(256, 2) void bwd_grad_kernel(BwdParams p, int n_dkd
   constexpr int B1 = DkdvLds<D, NK, BMK, 1, VLDS>::BYTES, B2 = DqLds<D, NQ, BNQ>::BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char lds[B1 > B2 ? B1 : B2];
   const int id = blockIdx.x;
-  int bh, r;
+  int bh, r, split;
   if (id < n_dkdv) {
-    tile_item(id, p.BH, bh, r);
+    tile_item(id, p.BH, 1, bh, r, split);
     dkdv_body<D, NK, BMK, 1, VLDS>(p, bh, r, lds);
   } else {
-    tile_item(id - n_dkdv, p.BH, bh, r);
+    tile_item(id - n_dkdv, p.BH, 1, bh, r, split);
     dq_body<D, NQ, RQ, BNQ>(p, bh, n_qtiles - 1 - r, lds);
   }
 }

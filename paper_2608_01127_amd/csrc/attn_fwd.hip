@@ -1,11 +1,10 @@
 // Block-causal attention forward and cached chunk attention (gfx950).
 //
-// One workgroup computes 256 query rows of one (batch, head): 4 waves of two
-// 32-row blocks at D = 64, 8 waves of one 32-row block at D = 72 and 128
-// (FwdCfg).  Cached attention with at most 512 queued rows runs 64- or
-// 128-row workgroups whose 8 waves split each key step into key groups
-// (FwdDecodeCfg).  Keys are visited in steps of 64 (128 for the key-group
-// configurations); each step stages the K and V tile in LDS once for all the
+// One workgroup computes 64, 128 or 256 query rows of one (batch, head), 32 or
+// 64 per wave (FwdTile: larger tiles for grids that fill the card, 64-row ones
+// whose waves split each key step into key groups for those that do not, and
+// for cached attention with few queued rows).  Keys are visited in steps of 64
+// or 128; each step stages the K and V tile in LDS once for all the
 // waves.  Per wave, 32-row block and 32-key block:
 //   S^T[key][q] = K Q^T              (bf16 MFMA 32x32x16, fp32 accumulate;
 //                                     Q stays in registers as the B operand)
@@ -120,11 +119,6 @@ __device__ __forceinline__ void stage_kv(const FwdParams& p, int bh, long long k
 // O rescale is skipped on almost every step.
 constexpr float kRescaleThreshold = 8.f;
 
-// K/V stages of a configuration: two (double buffering) except for the
-// four-wave key-group configuration of 64 queued rows, which streams 64-key
-// tiles four deep.
-constexpr int fwd_stages(int nw, int kg) { return kg > 1 && nw == 4 ? 4 : 2; }
-
 // NW waves per workgroup, each owning RB blocks of 32 query rows; BN keys per
 // main-loop step.  With RB = 2 every K and V fragment read from LDS feeds two
 // MFMAs (one per row block), halving LDS traffic per MFMA: with one 32-row
@@ -134,8 +128,10 @@ constexpr int fwd_stages(int nw, int kg) { return kg > 1 && nw == 4 ? 4 : 2; }
 // KG * BN keys and group g works on its BN-key slice, so KG groups cover
 // different keys of the same query rows and merge (m, l, O) through LDS at
 // the end.  With few query rows this keeps all four SIMDs of a CU busy.
-template <int D, bool CACHED, int NW, int BN, int RB, int KG>
-__global__ __launch_bounds__(64 * NW, (8 / NW) > 0 ? (8 / NW) : 1) void attn_fwd_kernel(FwdParams p) {
+// NSTG K/V stages: two (double buffering), or four where a call is bound by
+// streaming the keys.  WPS: waves per SIMD the registers are allocated for.
+template <int D, bool CACHED, int NW, int BN, int RB, int KG, int NSTG, int WPS>
+__global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
   static_assert(NW % KG == 0, "waves split evenly into key groups");
   constexpr int NWR = NW / KG;           // waves per key group (row waves)
   constexpr int BM = 32 * RB * NWR, NT = 64 * NW, KB = BN / 32;
@@ -143,7 +139,6 @@ __global__ __launch_bounds__(64 * NW, (8 / NW) > 0 ? (8 / NW) : 1) void attn_fwd
   constexpr int KK = (D + 15) / 16;  // contraction steps over D (D = 72: the last one half zeros)
   constexpr int DB = (D + 31) / 32;  // 32-wide column blocks of D (D = 72: the last one 8 wide)
   constexpr int TE = stage_elems<D, BK, NT>();  // elements of one staged tile buffer
-  constexpr int NSTG = fwd_stages(NW, KG);      // K/V stages (see the main loop)
   __shared__ __attribute__((aligned(16))) bf16_t lds[2][NSTG][TE];  // K, V x stages
   bf16_t(*Ks)[TE] = lds[0];
   bf16_t(*Vs)[TE] = lds[1];
@@ -154,10 +149,9 @@ __global__ __launch_bounds__(64 * NW, (8 / NW) > 0 ? (8 / NW) : 1) void attn_fwd
     cached_item(blockIdx.x, gridDim.x, p.n_qtiles, NS, p.n_whole, bh, qt, split, nst);
   } else {
     int rank;
-    tile_item(blockIdx.x, p.BH, bh, rank);
+    tile_item(blockIdx.x, p.BH, NS, bh, rank, split);
     qt = p.n_qtiles - 1 - rank;  // later query tiles see more keys
-    split = 0;
-    nst = 1;
+    nst = NS;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rw = wave % NWR, kg = wave / NWR;  // row wave, key group
@@ -373,7 +367,13 @@ __global__ __launch_bounds__(64 * NW, (8 / NW) > 0 ? (8 / NW) : 1) void attn_fwd
         const int r0 = (rw * RB + rb) * 32;  // this row block within the Q tile
         const bf16_t* qs = r0 < 64 ? Ks[NSTG - 1] : Vs[NSTG - 1];
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) qf[rb][kk] = fq.row8(qs, r0 & 63, kk);
+        for (int kk = 0; kk < KK; ++kk) {
+          qf[rb][kk] = fq.row8(qs, r0 & 63, kk);
+          if (D % 16 != 0 && 16 * kk + 8 * (lane >> 5) >= D) {  // columns past D contribute zeros
+#pragma unroll
+            for (int j = 0; j < 8; ++j) qf[rb][kk][j] = (__bf16)0.f;
+          }
+        }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
@@ -529,38 +529,42 @@ __global__ __launch_bounds__(64 * NW, (8 / NW) > 0 ? (8 / NW) : 1) void attn_fwd
   }
 }
 
-// Tile configuration per head dimension: waves per workgroup (32 query rows
-// each), keys per step, row blocks per wave and LDS stages.  With D = 128 a
-// workgroup of 8 waves shares each staged K/V tile among 256 queries, halving
-// L2 -> LDS traffic per MFMA; with D = 64 four waves of two row blocks (two
-// workgroups per CU) measured faster.
+// Tile configurations.  A configuration is bound by how many workgroups the
+// grid gives the 256 CUs, then by the SIMDs' issue (softmax VALU work and
+// MFMAs), with the staging traffic per MFMA growing as the tile shrinks.
+template <int NW_, int BN_, int RB_, int KG_, int NSTG_, int WPS_>
+struct FwdTile {
+  static constexpr int NW = NW_, BN = BN_, RB = RB_, KG = KG_, NSTG = NSTG_, WPS = WPS_;
+  static constexpr int BM = 32 * RB * (NW / KG);  // query rows per workgroup
+  static constexpr int BK = BN * KG;              // keys per step
+};
+// 256 rows.  D = 128: eight waves share each staged K/V tile (240 registers,
+// one workgroup per CU).  D = 64 (cached calls): four waves of two row blocks.
+using Rows256 = FwdTile<8, 64, 1, 1, 2, 1>;
+using Rows256x2 = FwdTile<4, 64, 2, 1, 2, 2>;
+// 128 rows, four waves.  D = 64 and 72 at three waves per SIMD (<= 168
+// registers): D = 72 training (16 heads x 19200) 1098 -> 1037 us against eight
+// waves of 256 rows, whose barriers hold two waves per SIMD in step; D = 64
+// (24 heads x 10560) 439 -> 433 against two row blocks per wave, (24 x 4000)
+// 95 -> 81.  D = 128 at two.
 template <int D>
-struct FwdCfg {
-  static constexpr int NW = D == 64 ? 4 : 8;
-  static constexpr int BN = 64;
-  static constexpr int RB = D == 64 ? 2 : 1;  // 32-row query blocks per wave
-  static constexpr int KG = 1;
-};
-// (D = 72, the 0.5B model's head width, runs the D = 128 arrangement: its
-// wider accumulators leave no room for two row blocks per wave.)
-
+using Rows128 = FwdTile<4, 64, 1, 1, 2, D == 128 ? 2 : 3>;
+// 64 rows, four waves in two key groups, 64 keys per step: half the rows and
+// half the chain of key steps per wave, for grids that leave CUs idle.
+template <int D>
+using Rows64 = FwdTile<4, 32, 1, 2, 2, D == 128 ? 2 : 3>;
+// 64 rows, eight waves in four key groups, 128 keys per step.
+using Rows64x8 = FwdTile<8, 32, 1, 4, 2, 2>;
 // Cached attention with few queued rows (a short chunk over a long window) is
-// bound by streaming the window from HBM.  The waves split into key groups of
-// row waves: for 64 rows, four waves in 2 groups of 2 stage 64 keys per step,
-// four stages deep (one wave per SIMD; measured 3-4% faster than eight waves
-// in 4 groups double-buffering 128-key steps, whose bulk waits leave the
-// memory pipe idle between steps); for 128 rows, eight waves in 2 groups of 4
-// stage 128 keys per step, double-buffered.
-// Up to 512 queued rows run as 128-row tiles of this kind (their workgroups read
-// the same window, which the L2 and the Infinity Cache share): measured 20% and
-// 11% faster than 256-row tiles at 256 and 512 rows over a 6 x 2640-token window.
-template <int D, int NWR>
-struct FwdDecodeCfg {
-  static constexpr int NW = NWR == 2 ? 4 : 8;
-  static constexpr int KG = NW / NWR;
-  static constexpr int BN = NWR == 2 ? 32 : 128 / KG;
-  static constexpr int RB = 1;
-};
+// bound by streaming the window from HBM.  64 rows: the same key groups with
+// four stages in flight (measured 3-4% faster than eight waves in 4 groups
+// double-buffering 128-key steps, whose bulk waits leave the memory pipe idle
+// between steps).  128 rows (D = 128): eight waves in 2 groups of 4 stage 128
+// keys per step; their workgroups read the same window, which the L2 and the
+// Infinity Cache share: measured 20% and 11% faster than 256-row tiles at 256
+// and 512 rows over a 6 x 2640-token window.
+using Stream64 = FwdTile<4, 32, 1, 2, 4, 2>;
+using Stream128 = FwdTile<8, 64, 1, 2, 2, 1>;
 
 // Merge of the per-split partials: with M = max_s m_s and w_s = 2^(m_s - M),
 //   O = sum_s w_s O_s / sum_s w_s l_s,   LSE = (M + log2 sum_s w_s l_s) ln 2.
@@ -640,20 +644,24 @@ static hipError_t launch_combine_d(const FwdParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int D, bool CACHED, int NW, int BN, int RB, int KG>
-static hipError_t launch_fwd_tpl(FwdParams p, hipStream_t stream) {
-  constexpr int BM = 32 * RB * (NW / KG);
-  const long long grid = fwd_prepare(p, BM, CACHED);
-  hipLaunchKernelGGL((attn_fwd_kernel<D, CACHED, NW, BN, RB, KG>), dim3((unsigned)grid), dim3(64 * NW), 0, stream, p);
+template <int D, bool CACHED, class C>
+static hipError_t launch_tile(FwdParams p, hipStream_t stream) {
+  const long long grid = fwd_prepare(p, C::BM, CACHED);
+  hipLaunchKernelGGL((attn_fwd_kernel<D, CACHED, C::NW, C::BN, C::RB, C::KG, C::NSTG, C::WPS>), dim3((unsigned)grid),
+                     dim3(64 * C::NW), 0, stream, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.n_splits == 1) return e;
   return launch_combine_d<D>(p, stream);
 }
 
-template <int D, bool CACHED>
-static hipError_t launch_fwd_cfg(const FwdParams& p, hipStream_t stream) {
-  using C = FwdCfg<D>;
-  return launch_fwd_tpl<D, CACHED, C::NW, C::BN, C::RB, C::KG>(p, stream);
+// Configuration of a cached call with its workgroups resident per CU (`fallback`
+// where no device is present) and the workgroups per CU that a call bound by
+// streaming its keys is spread over.
+template <int D, class C>
+static FwdChoice cached_choice(int fallback, int stream_wgs) {
+  static const int n = resident_workgroups(
+      attn_fwd_kernel<D, true, C::NW, C::BN, C::RB, C::KG, C::NSTG, C::WPS>, 64 * C::NW, fallback);
+  return {C::BM, C::BK, n, stream_wgs};
 }
 
 // This file is compiled once per head dimension (MW_FWD_HEAD_DIM = 64, 72 or 128),
@@ -663,75 +671,81 @@ static hipError_t launch_fwd_cfg(const FwdParams& p, hipStream_t stream) {
 // (MW_FWD_CACHED) with 64-byte loop alignment (measured 2-4% faster on the
 // cached calls, and 1.7% slower on the training kernel, which therefore stays
 // in the main unit), and the key-group configurations for few queued rows
-// (MW_FWD_DECODE) with the default scheduler.
-template <int D, bool CACHED, int NW, int BN, int RB, int KG>
-static int resident_tpl(int fallback) {
-  static const int n = resident_workgroups(attn_fwd_kernel<D, CACHED, NW, BN, RB, KG>, 64 * NW, fallback);
-  return n;
+// (MW_FWD_DECODE) with the default scheduler.  The D = 128 tiles for
+// grids that do not fill the card (MW_FWD_SMALL) have a unit of their own too:
+// sharing one with the 256-row training kernel moves its loop relative to the
+// instruction-cache lines, which cost it 1.7%.
+//
+// Training calls pick their tile by grid_fill; so do cached calls without a
+// key-range split up to 512 tiles (unsplit_fill), on heads and keys only: over
+// a whole history they visit the keys in the training call's order and give
+// its rows bit for bit.
+#if MW_FWD_HEAD_DIM != 128
+#define MW_CAT_(a, b) a##b
+#define MW_CAT(a, b) MW_CAT_(a, b)
+constexpr int kD = MW_FWD_HEAD_DIM;
+// Cached calls of more than 64 rows: 128-row tiles, except long queues at D = 64
+using CachedLong = std::conditional_t<kD == 64, Rows256x2, Rows128<kD>>;
+hipError_t MW_CAT(launch_fwd_, MW_FWD_HEAD_DIM)(const FwdParams& p, bool cached, hipStream_t stream) {
+  const GridFill fill = cached ? unsplit_fill(kD, p.BH, p.Tk) : grid_fill(kD, p.BH, p.Tk);
+  if (!cached) {
+    if (fill == GridFill::sparse) return launch_tile<kD, false, Rows64x8>(p, stream);
+    if (fill == GridFill::small) return launch_tile<kD, false, Rows64<kD>>(p, stream);
+    return launch_tile<kD, false, Rows128<kD>>(p, stream);
+  }
+  if (p.Tq <= 64) return launch_tile<kD, true, Stream64>(p, stream);
+  if (p.n_splits <= 1 && fill == GridFill::sparse) return launch_tile<kD, true, Rows64x8>(p, stream);
+  if (p.n_splits <= 1 && fill == GridFill::small) return launch_tile<kD, true, Rows64<kD>>(p, stream);
+  if (p.Tq <= 512) return launch_tile<kD, true, Rows128<kD>>(p, stream);
+  return launch_tile<kD, true, CachedLong>(p, stream);
 }
-
-template <int D, bool CACHED>
-static int resident_cfg(int fallback) {
-  using C = FwdCfg<D>;
-  return resident_tpl<D, CACHED, C::NW, C::BN, C::RB, C::KG>(fallback);
+// (fallbacks, as built: Stream64 holds 64 KB of LDS at D = 64 and 96 KB at 72)
+FwdChoice MW_CAT(fwd_choice_, MW_FWD_HEAD_DIM)(int Tq) {
+  if (Tq <= 64) return cached_choice<kD, Stream64>(kD == 64 ? 2 : 1, 1);
+  if (Tq <= 512) return cached_choice<kD, Rows128<kD>>(3, 3);
+  return cached_choice<kD, CachedLong>(kD == 64 ? 2 : 3, kD == 64 ? 1 : 3);
 }
-
-// (fallbacks: D = 64 runs 4 waves of about 235 registers, two workgroups per
-// CU; D = 72 and 128 run 8 waves of 160-240 registers, one per CU)
-#if MW_FWD_HEAD_DIM == 64 && !defined(MW_FWD_DECODE)
-hipError_t launch_fwd_64(const FwdParams& p, bool cached, hipStream_t stream) {
-  return cached ? launch_fwd_cfg<64, true>(p, stream) : launch_fwd_cfg<64, false>(p, stream);
-}
-int fwd_resident_wgs_64(bool cached) { return cached ? resident_cfg<64, true>(2) : resident_cfg<64, false>(2); }
-#elif MW_FWD_HEAD_DIM == 72 && !defined(MW_FWD_DECODE)
-hipError_t launch_fwd_72(const FwdParams& p, bool cached, hipStream_t stream) {
-  return cached ? launch_fwd_cfg<72, true>(p, stream) : launch_fwd_cfg<72, false>(p, stream);
-}
-int fwd_resident_wgs_72(bool cached) { return cached ? resident_cfg<72, true>(1) : resident_cfg<72, false>(1); }
-#elif MW_FWD_HEAD_DIM == 128 && !defined(MW_FWD_DECODE) && !defined(MW_FWD_CACHED)
-int fwd_resident_wgs_128(bool cached) { return cached ? fwd_resident_wgs_cached_128() : resident_cfg<128, false>(1); }
+#elif !defined(MW_FWD_DECODE) && !defined(MW_FWD_CACHED) && !defined(MW_FWD_SMALL)
 hipError_t launch_fwd_128(const FwdParams& p, bool cached, hipStream_t stream) {
-  if (!cached) return launch_fwd_cfg<128, false>(p, stream);
-  const int bm = fwd_choice(128, true, p.Tq).bm;
-  if (bm != 32 * FwdCfg<128>::RB * FwdCfg<128>::NW) return launch_fwd_decode_128(p, bm, stream);
+  const GridFill fill = cached ? unsplit_fill(128, p.BH, p.Tk) : grid_fill(128, p.BH, p.Tk);
+  if (!cached) {
+    if (fill != GridFill::full) return launch_fwd_small_128(p, fill, false, stream);
+    return launch_tile<128, false, Rows256>(p, stream);
+  }
+  if (p.Tq <= 512) return launch_fwd_decode_128(p, stream);
+  if (p.n_splits <= 1 && fill != GridFill::full) return launch_fwd_small_128(p, fill, true, stream);
   return launch_fwd_cached_128(p, stream);
 }
-#elif MW_FWD_HEAD_DIM == 128 && defined(MW_FWD_CACHED)
-hipError_t launch_fwd_cached_128(const FwdParams& p, hipStream_t stream) {
-  return launch_fwd_cfg<128, true>(p, stream);
-}
-int fwd_resident_wgs_cached_128() { return resident_cfg<128, true>(1); }
-#elif MW_FWD_HEAD_DIM == 128 && defined(MW_FWD_DECODE)
-hipError_t launch_fwd_decode_128(const FwdParams& p, int bm, hipStream_t stream) {
-  if (bm == 64) {
-    using C = FwdDecodeCfg<128, 2>;
-    return launch_fwd_tpl<128, true, C::NW, C::BN, C::RB, C::KG>(p, stream);
+#elif defined(MW_FWD_SMALL)
+hipError_t launch_fwd_small_128(const FwdParams& p, GridFill fill, bool cached, hipStream_t stream) {
+  if (cached) {
+    if (fill == GridFill::sparse) return launch_tile<128, true, Rows64x8>(p, stream);
+    return launch_tile<128, true, Rows64<128>>(p, stream);
   }
-  using C = FwdDecodeCfg<128, 4>;
-  return launch_fwd_tpl<128, true, C::NW, C::BN, C::RB, C::KG>(p, stream);
+  if (fill == GridFill::sparse) return launch_tile<128, false, Rows64x8>(p, stream);
+  if (fill == GridFill::small) return launch_tile<128, false, Rows64<128>>(p, stream);
+  return launch_tile<128, false, Rows128<128>>(p, stream);
+}
+#elif defined(MW_FWD_CACHED)
+hipError_t launch_fwd_cached_128(const FwdParams& p, hipStream_t stream) {
+  return launch_tile<128, true, Rows256>(p, stream);
+}
+FwdChoice fwd_choice_cached_128() { return cached_choice<128, Rows256>(1, 1); }
+#else
+hipError_t launch_fwd_decode_128(const FwdParams& p, hipStream_t stream) {
+  return p.Tq <= 64 ? launch_tile<128, true, Stream64>(p, stream) : launch_tile<128, true, Stream128>(p, stream);
 }
 // (fallback: 4 or 8 waves of 180-245 registers and 128 KB of LDS, one per CU)
-int fwd_resident_wgs_decode_128(int bm) {
-  using C2 = FwdDecodeCfg<128, 2>;
-  using C4 = FwdDecodeCfg<128, 4>;
-  return bm == 64 ? resident_tpl<128, true, C2::NW, C2::BN, C2::RB, C2::KG>(1)
-                  : resident_tpl<128, true, C4::NW, C4::BN, C4::RB, C4::KG>(1);
+FwdChoice fwd_choice_decode_128(int Tq) {
+  return Tq <= 64 ? cached_choice<128, Stream64>(1, 1) : cached_choice<128, Stream128>(1, 1);
 }
-#else
-#error "compile with -DMW_FWD_HEAD_DIM=64, 72 or 128 (128 optionally with -DMW_FWD_CACHED or -DMW_FWD_DECODE)"
 #endif
 
-#if MW_FWD_HEAD_DIM == 128 && !defined(MW_FWD_DECODE) && !defined(MW_FWD_CACHED)
-// Must agree with the dispatch in launch_fwd_128.
-FwdChoice fwd_choice(int D, bool cached, int Tq) {
-  using C2 = FwdDecodeCfg<128, 2>;
-  using C4 = FwdDecodeCfg<128, 4>;
-  if (cached && D == 128 && Tq <= 64) return {64, C2::BN * C2::KG, fwd_resident_wgs_decode_128(64)};
-  if (cached && D == 128 && Tq <= 512)  // 128-row tiles up to 512 rows
-    return {128, C4::BN * C4::KG, fwd_resident_wgs_decode_128(128)};
-  if (D == 64) return {32 * FwdCfg<64>::RB * FwdCfg<64>::NW, FwdCfg<64>::BN, fwd_resident_wgs_64(cached)};
-  if (D == 72) return {32 * FwdCfg<72>::RB * FwdCfg<72>::NW, FwdCfg<72>::BN, fwd_resident_wgs_72(cached)};
-  return {32 * FwdCfg<128>::RB * FwdCfg<128>::NW, FwdCfg<128>::BN, fwd_resident_wgs_128(cached)};
+#if MW_FWD_HEAD_DIM == 128 && !defined(MW_FWD_DECODE) && !defined(MW_FWD_CACHED) && !defined(MW_FWD_SMALL)
+FwdChoice fwd_choice(int D, int Tq) {
+  if (D == 64) return fwd_choice_64(Tq);
+  if (D == 72) return fwd_choice_72(Tq);
+  return Tq <= 512 ? fwd_choice_decode_128(Tq) : fwd_choice_cached_128();
 }
 
 hipError_t launch_combine(const FwdParams& p, int D, hipStream_t stream) {
@@ -754,7 +768,7 @@ int fwd_split_rows(int bm, int Tq, const SplitPlan& sp) {
 constexpr double kBf16Flops = 1.1e15;
 
 SplitPlan fwd_plan_cached(int D, int BH, int Tq, int Tk, int qlen, bool isolated, size_t ws_bytes) {
-  return fwd_plan_splits(fwd_choice(D, true, Tq), kBf16Flops, 2, D, BH, Tq, Tk, qlen, isolated, ws_bytes);
+  return fwd_plan_splits(fwd_choice(D, Tq), kBf16Flops, 2, D, BH, Tq, Tk, qlen, isolated, ws_bytes);
 }
 
 namespace {
@@ -792,12 +806,12 @@ double split_makespan(const std::vector<int>& steps, int heads, int slots, int n
 }
 
 struct PlanKey {
-  int bm, bk, wg, kv_bytes, D, BH, Tq, Tk, qlen, isolated;
+  int bm, bk, wg, swg, kv_bytes, D, BH, Tq, Tk, qlen, isolated;
   double flops;
   size_t ws;
   bool operator<(const PlanKey& o) const {
-    return std::tie(bm, bk, wg, kv_bytes, D, BH, Tq, Tk, qlen, isolated, flops, ws) <
-           std::tie(o.bm, o.bk, o.wg, o.kv_bytes, o.D, o.BH, o.Tq, o.Tk, o.qlen, o.isolated, o.flops, o.ws);
+    return std::tie(bm, bk, wg, swg, kv_bytes, D, BH, Tq, Tk, qlen, isolated, flops, ws) <
+           std::tie(o.bm, o.bk, o.wg, o.swg, o.kv_bytes, o.D, o.BH, o.Tq, o.Tk, o.qlen, o.isolated, o.flops, o.ws);
   }
 };
 
@@ -821,7 +835,7 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
     // streaming-bound (few query rows): every tile split, priced by CU coverage
     for (int ns = 1; ns <= ns_max; ++ns) {
       if (ns > 1 && fwd_split_bytes(D, BH, Tq, ns) > ws_bytes) break;
-      cands.push_back({t_stream / std::min(1.0, base * ns / cus) + part_time(Tq, ns), {ns, 0}});
+      cands.push_back({t_stream / std::min(1.0, base * ns / (cus * ch.stream_wgs)) + part_time(Tq, ns), {ns, 0}});
     }
   } else if (base >= 8.0 * slots) {
     // eight or more rounds of workgroups: the last round is a small fraction
@@ -893,7 +907,7 @@ SplitPlan fwd_plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D
   if (BH < 1 || Tq < 1 || Tk < 1 || qlen < 1 || ch.bm < 1 || ch.bk < 1) return {1, 0};
   static std::mutex mu;
   static std::map<PlanKey, SplitPlan> memo;
-  const PlanKey key{ch.bm, ch.bk, ch.wg_per_cu, kv_bytes, D, BH, Tq, Tk, qlen, isolated ? 1 : 0, flops, ws_bytes};
+  const PlanKey key{ch.bm, ch.bk, ch.wg_per_cu, ch.stream_wgs, kv_bytes, D, BH, Tq, Tk, qlen, isolated ? 1 : 0, flops, ws_bytes};
   {
     std::lock_guard<std::mutex> lock(mu);
     auto it = memo.find(key);

@@ -535,7 +535,7 @@ size_t mw_chunk_attn_cached_workspace_size(const mw_kvcache* c, int n_queued, in
   const int bh = c->B * c->H;
   // the larger of the two visibility rules' plans (a call given less workspace
   // plans within it)
-  const mw::FwdChoice ch = c->elem_bytes == 1 ? mw::fwd8_choice((int)tq) : mw::fwd_choice(c->D, true, (int)tq);
+  const mw::FwdChoice ch = c->elem_bytes == 1 ? mw::fwd8_choice((int)tq) : mw::fwd_choice(c->D, (int)tq);
   size_t bytes = 0;
   for (const bool isolated : {false, true}) {
     const mw::SplitPlan sp =

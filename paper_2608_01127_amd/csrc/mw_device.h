@@ -381,8 +381,8 @@ __device__ __forceinline__ int xcd_remap(int bid, int n) {
   return (bid % 8) * (n / 8) + bid / 8;
 }
 
-// Work order of the training grids.  Workgroup `bid` of n = BH * ntiles gets
-// (batch*head, tile rank), rank 0 being the heaviest tile of its head.
+// Work order of the training grids.  Workgroup `bid` of n = BH * ntiles * NS
+// gets (batch*head, tile rank, key range), rank 0 being the heaviest tile of its head.
 // Workgroup ids are dealt to the 8 XCDs round-robin.  With g the largest power
 // of two up to 8 that divides BH, the XCDs x with the same x mod g share BH / g
 // whole heads, so that a head's K/V stay in 8 / g L2s, and take their tiles
@@ -393,12 +393,17 @@ __device__ __forceinline__ int xcd_remap(int bid, int n) {
 // and backward 4063 -> 3620, 15 heads x 2999 (D = 72, g = 1) backward 121 -> 104;
 // at g = 8 a simulation of the D = 64 training shape's dispatch gives a 23%
 // shorter makespan.
-__device__ __forceinline__ void tile_item(int bid, int BH, int& bh, int& rank) {
+// With NS key ranges per tile (1 in training) a tile's ranges are neighbours.
+// (The 256-row D = 128 forward, whose loop the scheduler lays out anew with every
+// change around it, measured 1% faster with NS kept general than fixed to 1.)
+__device__ __forceinline__ void tile_item(int bid, int BH, int NS, int& bh, int& rank, int& split) {
   const int low = BH & -BH, g = low < 8 ? low : 8;  // 1, 2, 4 or 8
-  const int x = bid & 7, group = x & (g - 1), hpg = BH / g;
-  const int j = (bid >> 3) * (8 / g) + x / g;  // the group's j-th workgroup
-  rank = j / hpg;
-  bh = group * hpg + (j - rank * hpg);
+  const int x = bid % 8, group = x & (g - 1), hpg = BH / g;
+  const int j = (bid / 8) * (8 / g) + x / g;  // the group's j-th workgroup
+  const int r = j / (hpg * NS), rem = j - r * (hpg * NS);
+  bh = group * hpg + rem / NS;
+  rank = r;
+  split = rem % NS;
 }
 
 // Cached attention: the heads one after another on each XCD (xcd_remap).

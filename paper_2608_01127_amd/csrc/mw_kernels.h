@@ -89,31 +89,62 @@ struct BwdParams {
 hipError_t launch_fwd_64(const FwdParams& p, bool cached, hipStream_t stream);
 hipError_t launch_fwd_72(const FwdParams& p, bool cached, hipStream_t stream);
 hipError_t launch_fwd_128(const FwdParams& p, bool cached, hipStream_t stream);
-// cached attention at D = 128: the 256-row configuration, and the ones with
-// `bm` (64 or 128) query rows per workgroup
+// cached attention at D = 128: the 256-row configuration, and the few-row ones
 hipError_t launch_fwd_cached_128(const FwdParams& p, hipStream_t stream);
-hipError_t launch_fwd_decode_128(const FwdParams& p, int bm, hipStream_t stream);
+hipError_t launch_fwd_decode_128(const FwdParams& p, hipStream_t stream);
+// the D = 128 tiles for grids that do not fill the card
+enum class GridFill;
+hipError_t launch_fwd_small_128(const FwdParams& p, GridFill fill, bool cached, hipStream_t stream);
 inline hipError_t launch_fwd(const FwdParams& p, int D, bool cached, hipStream_t stream) {
   return D == 64 ? launch_fwd_64(p, cached, stream)
                  : (D == 72 ? launch_fwd_72(p, cached, stream) : launch_fwd_128(p, cached, stream));
 }
-// Workgroups per CU that the forward kernel of each unit holds at once
-// (runtime occupancy; the value the kernels' register and LDS use gives as
-// built where no device is present): the training or cached kernel of
-// launch_fwd_64 / _72 / _128, and the few-rows kernel of `bm` rows.
-int fwd_resident_wgs_64(bool cached);
-int fwd_resident_wgs_72(bool cached);
-int fwd_resident_wgs_128(bool cached);
-int fwd_resident_wgs_cached_128();
-int fwd_resident_wgs_decode_128(int bm);
 // Query rows per workgroup, keys per main-loop step and resident workgroups
-// per CU of the tile configuration the forward launcher picks for a shape.
+// per CU (runtime occupancy; the value the kernel's register and LDS use gives
+// as built where no device is present) of the tile configuration the launcher
+// picks for a cached call of Tq queued rows.
 struct FwdChoice {
   int bm;
   int bk;
   int wg_per_cu;
+  int stream_wgs;  // workgroups per CU that a call bound by streaming its keys is spread over
 };
-FwdChoice fwd_choice(int D, bool cached, int Tq);
+FwdChoice fwd_choice(int D, int Tq);
+FwdChoice fwd_choice_64(int Tq);
+FwdChoice fwd_choice_72(int Tq);
+FwdChoice fwd_choice_cached_128();
+FwdChoice fwd_choice_decode_128(int Tq);
+// How far a call without a key-range split fills the card, counted in 64-row
+// tiles of the key sequence (in training also the query sequence) over all
+// heads; the forward launchers pick their tile by it.  Measured on MI355X,
+// training forward, us, as (256-row | 128 | 64 | 64 in four key groups) where
+// a line was drawn:
+//   sparse  one eight-wave workgroup per CU, or up to 1.5 (2 at D = 64) where
+//           the sequence is long enough that half the tiles are light:
+//           D = 128, 1 x 8000 (183 | 143 | 96 | 76), 8 x 2200 (60 | - | 33 | 30),
+//           12 x 1500 (45 | - | 26 | 27); D = 64, 4 x 4000 (86 | 61 | 40 | 28).  A
+//           short sequence does not repay merging four groups: D = 128,
+//           8 x 600 (25 | - | 12 | 14); D = 64, 2 x 256 (13 | 7.5 | 5.4 | 5.9).
+//   small   up to 1.5 rounds of resident 64-row workgroups: D = 128, 24 x 2000
+//           (56 | 47 | 47); D = 72, 16 x 3000 (67 | 53 | 43), 24 x 3600 (94 | 90 | 90);
+//           D = 64, 24 x 3600 (89 | 76 | 69).
+//   mid     D = 128 up to three rounds of 128-row workgroups: 16 x 4800
+//           (131 | 118 | 130), 12 x 7200 (198 | 179 | 208), 12 x 9600 (300 | 314 | -).
+enum class GridFill { sparse, small, mid, full };
+inline GridFill grid_fill(int D, int BH, int Tk) {
+  const long long tiles = (long long)BH * ((Tk + 63) / 64);
+  if (tiles <= 256 && Tk >= (D == 128 ? 1536 : 512)) return GridFill::sparse;
+  if (tiles <= (D == 64 ? 512 : 384) && Tk >= 2048) return GridFill::sparse;
+  if (tiles <= (D == 128 ? 768 : (D == 72 ? 1152 : 1536))) return GridFill::small;
+  if (D == 128 && tiles <= 1536) return GridFill::mid;
+  return GridFill::full;
+}
+// A cached call without a key-range split takes the training forward's 64-row
+// tiles up to 512 of them (two a CU); from there on it keeps the tiles of the
+// split plans, whose whole tiles an unsplit call then gives bit for bit.
+inline GridFill unsplit_fill(int D, int BH, int Tk) {
+  return (long long)BH * ((Tk + 63) / 64) <= 512 ? grid_fill(D, BH, Tk) : GridFill::full;
+}
 // fp8 (e4m3) cached attention at D = 128: its tile configuration and launcher
 // (FwdParams as described above), and the merge of split partials (D = 128).
 FwdChoice fwd8_choice(int Tq);
