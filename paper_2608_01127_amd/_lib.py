@@ -8,6 +8,7 @@ exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 import os
 
@@ -140,8 +141,12 @@ def _torch():
 
 
 def _stream_handle(device) -> int:
+    """Handle of the current HIP stream of `device` (a device or its index)."""
     torch = _torch()
-    return torch.cuda.current_stream(device).cuda_stream
+    index = device if isinstance(device, int) else device.index
+    if index is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(index)  # current_stream() without its Stream object: 0.1 for 1.1 us
 
 
 def _ptr(t) -> int:
@@ -174,12 +179,31 @@ def _u8_4d(name, t):
         raise ValueError(f"{name} must be a contiguous [B,H,T,D] tensor on a GPU")
 
 
-def _strides(*ts):
-    """mw_strides array (B, H, T element strides) of the given [B,H,T,D] views."""
-    arr = (mw_strides * len(ts))()
-    for i, t in enumerate(ts):
-        arr[i] = mw_strides(t.stride(0), t.stride(1), t.stride(2))
+@functools.lru_cache(maxsize=512)
+def _strides_array(*strides):
+    arr = (mw_strides * len(strides))()
+    for i, s in enumerate(strides):
+        arr[i] = mw_strides(s[0], s[1], s[2])
     return arr
+
+
+def _strides(*ts):
+    """mw_strides array (B, H, T element strides) of the given [B,H,T,D] views.  The arrays are kept
+    by their values (the library only reads them): filling one takes 0.6 us a tensor."""
+    return _strides_array(*[t.stride() for t in ts])
+
+
+def _plain_views(ts, shape, index) -> bool:
+    """Whether every tensor is a bf16 [B,H,T,D] view of `shape` on GPU `index` with a contiguous
+    last dimension: what the checks below find one by one, in a sixth of their time.  A call
+    whose tensors are not goes through them, for their errors."""
+    if index < 0 or len(shape) != 4:
+        return False
+    bf16 = _torch().bfloat16
+    for t in ts:
+        if t.dtype is not bf16 or t.shape != shape or t.get_device() != index or t.stride()[-1] != 1:
+            return False
+    return True
 
 
 def _check_lse(lse, shape, dev) -> None:
@@ -206,19 +230,23 @@ def mw_block_causal_attn_fwd(q, k, v, chunk_len: int, scale=None, out=None, lse=
     """Block-causal attention forward.  q, k, v: bf16 [B,H,T,D] (views with a
     contiguous head dimension are read in place).  Returns (o, lse)."""
     torch = _torch()
-    for n, t in (("q", q), ("k", k), ("v", v)):
-        _bf16_4d(n, t, view=True)
-    if k.shape != q.shape or v.shape != q.shape:
-        raise ValueError("q, k, v must have the same shape")
+    plain = _plain_views((q, k, v) if out is None else (q, k, v, out), q.shape, q.get_device())
+    if not plain:
+        for n, t in (("q", q), ("k", k), ("v", v)):
+            _bf16_4d(n, t, view=True)
+        if k.shape != q.shape or v.shape != q.shape:
+            raise ValueError("q, k, v must have the same shape")
+        _same_device(q, k, v)
     B, H, T, D = q.shape
-    dev = _same_device(q, k, v)
+    dev = q.device
     scale = 1.0 / math.sqrt(D) if scale is None else float(scale)
     o = torch.empty_like(q) if out is None else out
     lse = torch.empty((B, H, T), dtype=torch.float32, device=dev) if lse is None else lse
-    _bf16_4d("out", o, view=True)
-    if o.shape != q.shape:
-        raise ValueError("out must have the shape of q")
-    _same_device(q, o)
+    if not plain:
+        _bf16_4d("out", o, view=True)
+        if o.shape != q.shape:
+            raise ValueError("out must have the shape of q")
+        _same_device(q, o)
     _check_lse(lse, (B, H, T), dev)
     _check(load().mw_block_causal_attn_fwd_strided(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
                                                    _strides(q, k, v, o), B, H, T, D, int(chunk_len), scale,
@@ -235,14 +263,16 @@ def mw_block_causal_attn_bwd(q, k, v, o, d_o, lse, chunk_len: int, scale=None, w
     """Backward of mw_block_causal_attn_fwd.  Returns (dq, dk, dv), bf16 [B,H,T,D]
     (views with a contiguous head dimension are accepted for every tensor)."""
     torch = _torch()
-    for n, t in (("q", q), ("k", k), ("v", v), ("o", o), ("d_o", d_o)):
-        _bf16_4d(n, t, view=True)
-        if t.shape != q.shape:
-            raise ValueError(f"{n} must have the shape of q")
+    plain = _plain_views([t for t in (q, k, v, o, d_o, dq, dk, dv) if t is not None], q.shape, q.get_device())
+    if not plain:
+        for n, t in (("q", q), ("k", k), ("v", v), ("o", o), ("d_o", d_o)):
+            _bf16_4d(n, t, view=True)
+            if t.shape != q.shape:
+                raise ValueError(f"{n} must have the shape of q")
     B, H, T, D = q.shape
     if lse.shape != (B, H, T) or lse.dtype != torch.float32 or not lse.is_contiguous():
         raise ValueError("lse must be fp32 [B,H,T] contiguous")
-    dev = _same_device(q, k, v, o, d_o, lse)
+    dev = _same_device(q, lse) if plain else _same_device(q, k, v, o, d_o, lse)
     scale = 1.0 / math.sqrt(D) if scale is None else float(scale)
     need = mw_block_causal_attn_bwd_workspace_size(B, H, T, D)
     if workspace is None:
@@ -250,10 +280,11 @@ def mw_block_causal_attn_bwd(q, k, v, o, d_o, lse, chunk_len: int, scale=None, w
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(q) if dk is None else dk
     dv = torch.empty_like(q) if dv is None else dv
-    for n, t in (("dq", dq), ("dk", dk), ("dv", dv)):
-        _bf16_4d(n, t, view=True)
-        if t.shape != q.shape:
-            raise ValueError(f"{n} must have the shape of q")
+    if not plain:
+        for n, t in (("dq", dq), ("dk", dk), ("dv", dv)):
+            _bf16_4d(n, t, view=True)
+            if t.shape != q.shape:
+                raise ValueError(f"{n} must have the shape of q")
     _same_device(q, workspace, dq, dk, dv)
     nbytes = workspace.numel() * workspace.element_size()
     _check(load().mw_block_causal_attn_bwd_strided(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(d_o), _ptr(lse),
@@ -358,11 +389,13 @@ def mw_kvcache_append(cache: KVCache, k_chunk, v_chunk) -> int:
     """Commit one chunk (bf16 [B,H,L,D], or a view of one with a contiguous head
     dimension); returns the slot it was written to."""
     d = cache.desc
-    for n, t in (("k_chunk", k_chunk), ("v_chunk", v_chunk)):
-        _bf16_4d(n, t, view=True)
-        if tuple(t.shape) != (d.B, d.H, d.L, d.D):
-            raise ValueError(f"{n} must be [B,H,L,D] = {(d.B, d.H, d.L, d.D)}")
-    dev = _same_device(cache.k_slots, k_chunk, v_chunk)
+    if not _plain_views((k_chunk, v_chunk), (d.B, d.H, d.L, d.D), cache.k_slots.get_device()):
+        for n, t in (("k_chunk", k_chunk), ("v_chunk", v_chunk)):
+            _bf16_4d(n, t, view=True)
+            if tuple(t.shape) != (d.B, d.H, d.L, d.D):
+                raise ValueError(f"{n} must be [B,H,L,D] = {(d.B, d.H, d.L, d.D)}")
+        _same_device(cache.k_slots, k_chunk, v_chunk)
+    dev = cache.k_slots.device
     _check(load().mw_kvcache_append_strided(ctypes.byref(d), _ptr(k_chunk), _ptr(v_chunk),
                                             _strides(k_chunk, v_chunk), _stream_handle(dev)))
     # the slot the library wrote: the newest committed chunk's, by the library's own rule
@@ -416,16 +449,21 @@ def mw_chunk_attn_cached(q, k_new, v_new, n_queued: int, q_len: int, cache: KVCa
     """
     torch = _torch()
     d = cache.desc
-    for n, t in (("q", q), ("k_new", k_new), ("v_new", v_new)):
-        _bf16_4d(n, t, view=True)
-        if tuple(t.shape) != (d.B, d.H, n_queued * q_len, d.D):
-            raise ValueError(f"{n} must be [B,H,n_queued*q_len,D] = {(d.B, d.H, n_queued * q_len, d.D)}")
-    dev = _same_device(cache.k_slots, q, k_new, v_new)
+    plain = _plain_views((q, k_new, v_new) if out is None else (q, k_new, v_new, out),
+                         (d.B, d.H, n_queued * q_len, d.D), cache.k_slots.get_device())
+    if not plain:
+        for n, t in (("q", q), ("k_new", k_new), ("v_new", v_new)):
+            _bf16_4d(n, t, view=True)
+            if tuple(t.shape) != (d.B, d.H, n_queued * q_len, d.D):
+                raise ValueError(f"{n} must be [B,H,n_queued*q_len,D] = {(d.B, d.H, n_queued * q_len, d.D)}")
+        _same_device(cache.k_slots, q, k_new, v_new)
+    dev = cache.k_slots.device
     scale = 1.0 / math.sqrt(d.D) if scale is None else float(scale)
     o = torch.empty_like(q) if out is None else out
-    _bf16_4d("out", o, view=True)
-    if o.shape != q.shape:
-        raise ValueError("out must have the shape of q")
+    if not plain:
+        _bf16_4d("out", o, view=True)
+        if o.shape != q.shape:
+            raise ValueError("out must have the shape of q")
     if want_lse and lse is None:
         lse = torch.empty((d.B, d.H, n_queued * q_len), dtype=torch.float32, device=dev)
     _check_lse(lse, (d.B, d.H, n_queued * q_len), dev)
