@@ -766,6 +766,9 @@ int fwd_split_rows(int bm, int Tq, const SplitPlan& sp) {
 
 // Sustained MFMA rate of the bf16 cached kernel assumed by the split planner.
 constexpr double kBf16Flops = 1.1e15;
+// Time of a streaming workgroup beside its key range: Q and the first tiles'
+// latency, the partials at the end.
+constexpr double kStreamWgTime = 3e-6;
 
 SplitPlan fwd_plan_cached(int D, int BH, int Tq, int Tk, int qlen, bool isolated, size_t ws_bytes) {
   return fwd_plan_splits(fwd_choice(D, Tq), kBf16Flops, 2, D, BH, Tq, Tk, qlen, isolated, ws_bytes);
@@ -832,10 +835,22 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
   };
   std::vector<Cand> cands;
   if (t_mfma < t_stream) {
-    // streaming-bound (few query rows): every tile split, priced by CU coverage
+    // streaming-bound (few query rows): every tile split, priced by the rounds
+    // of workgroups on the CUs, each the streaming of its key range at a CU's
+    // share of the bandwidth plus its prologue and epilogue.  (Pricing only the
+    // share of CUs covered took 11 ranges, 264 workgroups, for 24 heads: the
+    // last 8 ran a second round.  Calls over e4m3 keep that pricing: their
+    // probabilities are rounded against the reference of their own key range,
+    // so another split would move their outputs by a rounding of each.)
     for (int ns = 1; ns <= ns_max; ++ns) {
       if (ns > 1 && fwd_split_bytes(D, BH, Tq, ns) > ws_bytes) break;
-      cands.push_back({t_stream / std::min(1.0, base * ns / (cus * ch.stream_wgs)) + part_time(Tq, ns), {ns, 0}});
+      const double wgs = base * ns, room = cus * ch.stream_wgs;
+      double t = t_stream / std::min(1.0, wgs / room);
+      if (kv_bytes > 1) {
+        const double rounds = std::ceil(wgs / room);
+        t = rounds * (kStreamWgTime + t_stream * room / wgs);
+      }
+      cands.push_back({t + part_time(Tq, ns), {ns, 0}});
     }
   } else if (base >= 8.0 * slots) {
     // eight or more rounds of workgroups: the last round is a small fraction
@@ -891,8 +906,10 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
 // Split plan from a cost model, memoised per shape (a streaming loop repeats
 // its shape every step).  A call is bound by its MFMA time or by streaming
 // its K/V window, whichever is larger at full occupancy.  A streaming-bound
-// call splits every query tile and runs at the fraction of the 256 CUs its
-// grid covers (one workgroup per CU keeps a CU's loads in flight).  For an
+// call splits every query tile and takes as long as the rounds of its
+// workgroups on the CUs (a workgroup or a few per CU keep the loads in flight):
+// 24 heads, 64 rows over 6 x 2640 tokens, 64 -> 39 us at D = 128, 74 -> 32 at 72
+// and 55 -> 26 at 64 against pricing the share of CUs covered.  For an
 // MFMA-bound call a list-scheduling simulation of the dispatch order prices
 // every split count and whole-tile count: keeping the heaviest tiles whole and
 // splitting only the light ones that run last evens out the CUs' finish

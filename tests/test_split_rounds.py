@@ -1,0 +1,24 @@
+"""The key-range split of cached calls bound by streaming their window (host logic, no GPU): the
+workgroups fill whole rounds of the CUs for head counts that do not divide them."""
+import ctypes
+
+import pytest
+
+import paper_2608_01127_amd as mw
+from test_abi_host import new_cache
+
+
+@pytest.mark.parametrize("H,D,q_len,bm,per_cu", [(12, 128, 64, 64, 1), (24, 128, 64, 64, 1), (24, 128, 100, 128, 1),
+                                                 (36, 128, 33, 64, 1), (40, 64, 64, 64, 1), (24, 72, 17, 64, 1),
+                                                 (24, 72, 100, 128, 3), (20, 64, 128, 128, 3), (72, 128, 94, 128, 1)])
+def test_streaming_splits_fill_rounds(H, D, q_len, bm, per_cu):
+    lib = mw.load()
+    c = new_cache(S=8, B=1, H=H, L=2640, D=D)
+    c.head = 6
+    ns, nw = ctypes.c_int(), ctypes.c_int()
+    ws = lib.mw_chunk_attn_cached_workspace_size(ctypes.byref(c), 1, q_len, 6)
+    assert lib.mw_chunk_attn_cached_plan(ctypes.byref(c), 1, q_len, 6, mw.MW_QUEUED_CAUSAL, ws, ctypes.byref(ns),
+                                         ctypes.byref(nw)) == mw.MW_OK
+    wgs, room = H * -(-q_len // bm) * ns.value, 256 * per_cu
+    assert nw.value == 0 and wgs >= 0.75 * room * -(-wgs // room), (ns.value, wgs)
+    assert ns.value * H * q_len * (D + 2) * 4 <= ws
