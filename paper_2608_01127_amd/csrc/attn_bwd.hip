@@ -118,7 +118,7 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const int bh, cons
   static_assert(NW % QG == 0, "waves split evenly into query groups");
   constexpr int NWK = NW / QG, BN = 32 * NWK, NT = 64 * NW;
   static_assert(BM % 32 == 0, "32-row query blocks");
-  constexpr int KK = (D + 15) / 16, DB = (D + 31) / 32;  // D = 72: 80 and 96 columns
+  constexpr int KK = (D + 15) / 16, DB = D / 32;  // D = 72: 80 columns, and a tail of 8 (Tail72)
   static_assert(VL == 0 || (D % 16 == 0 && VL <= KK), "the V fragments in LDS have no zero columns past D");
   using LD = DkdvLds<D, NW, QG, BM, VL>;
   constexpr int TE = LD::TE, RT = LD::RT, BS = LD::BS;
@@ -160,6 +160,9 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const int bh, cons
       for (int j = 0; j < 8; ++j) kf[kk][j] = vf[kk][j] = (__bf16)0.f;
     }
   }
+  constexpr bool TAIL = D % 32 != 0;
+  const Tail72 ft(lane, gq * D);  // (TAIL)
+  f32x4 tail[4] = {zero4(), zero4(), zero4(), zero4()};  // (TAIL) dV^T of keys 0..15 and 16..31, dK^T of the same
   f32x16 dv[DB], dk[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) {
@@ -234,15 +237,28 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const int bh, cons
           dp[i] = pv * dp[i];  // P (dP - Delta)
         }
       }
+      bf16x8 pbs[2], dsbs[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const bf16x8 pb = pack8(s, t), dsb = pack8(dp, t);
+        pbs[t] = pb;
+        dsbs[t] = dsb;
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
           const bf16x8 dot = fo.tr8(dOt, qb * 32, t, db);
           dv[db] = mfma32(dot, pb, dv[db]);
           const bf16x8 qt = fo.tr8(Qt, qb * 32, t, db);
           dk[db] = mfma32(qt, dsb, dk[db]);
+        }
+      }
+      if constexpr (TAIL) {
+        const bf16x8 dot = ft.read(dOt, qb * 32), qt = ft.read(Qt, qb * 32);
+        tail_operands(pbs[0], pbs[1]);
+        tail_operands(dsbs[0], dsbs[1]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          tail[e] = mfma16(dot, pbs[e], tail[e]);
+          tail[2 + e] = mfma16(qt, dsbs[e], tail[2 + e]);
         }
       }
     }
@@ -279,7 +295,33 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const int bh, cons
     merge_groups<QG, NWK>(dv, qg, kw, lane, lds);
     __syncthreads();
     merge_groups<QG, NWK>(dk, qg, kw, lane, lds);
+    if constexpr (TAIL) {
+      f32x16 all[1];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) all[0][i] = tail[i / 4][i % 4];
+      __syncthreads();
+      merge_groups<QG, NWK>(all, qg, kw, lane, lds);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) tail[i / 4][i % 4] = all[0][i];
+    }
     if (qg > 0) return;  // no barrier follows
+  }
+  if constexpr (TAIL) {
+    if (lane < 32) {  // columns 64 + 4 (l / 16) + i of keys l % 16 and 16 + l % 16
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int key = k0 + kw * 32 + 16 * e + (lane & 15), col = 64 + 4 * (lane >> 4);
+        if (key >= T) continue;
+        bf16x4 wk, wv;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          wk[j] = to_bf16(tail[2 + e][j] * p.scale);
+          wv[j] = to_bf16(tail[e][j]);
+        }
+        *reinterpret_cast<bf16x4*>(p.dk + bi * p.sdk.b + hi * p.sdk.h + key * p.sdk.t + col) = wk;
+        *reinterpret_cast<bf16x4*>(p.dv + bi * p.sdv.b + hi * p.sdv.h + key * p.sdv.t + col) = wv;
+      }
+    }
   }
   if (mykey >= T) return;
   bf16_t* dkrow = p.dk + bi * p.sdk.b + hi * p.sdk.h + mykey * p.sdk.t;
@@ -295,7 +337,6 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const int bh, cons
         wv[j] = to_bf16(dv[db][4 * g + j]);
       }
       const int col = db * 32 + 8 * g + 4 * (lane >> 5);
-      if (D % 32 != 0 && col >= D) continue;  // (D = 72)
       *reinterpret_cast<bf16x4*>(dkrow + col) = wk;
       *reinterpret_cast<bf16x4*>(dvrow + col) = wv;
     }
@@ -317,7 +358,7 @@ template <int D, int NW, int KG, int BN>
 __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const int qt, unsigned char* lds) {
   static_assert(NW % KG == 0, "waves split evenly into key groups");
   constexpr int NWR = NW / KG, BM = 32 * NWR, NT = 64 * NW, BS = BN * KG;
-  constexpr int KK = (D + 15) / 16, DB = (D + 31) / 32;  // D = 72: 80 and 96 columns
+  constexpr int KK = (D + 15) / 16, DB = D / 32;  // D = 72: 80 columns, and a tail of 8 (Tail72)
   constexpr int TE = DqLds<D, NW, BS>::TE;
   bf16_t(*Ks)[TE] = reinterpret_cast<bf16_t(*)[TE]>(lds);
   bf16_t(*Vs)[TE] = reinterpret_cast<bf16_t(*)[TE]>(lds + 2 * TE * 2);
@@ -359,6 +400,9 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const 
 #pragma unroll
   for (int i = 0; i < 16; ++i) ndl[i] = ndlt;
 
+  constexpr bool TAIL = D % 32 != 0;
+  const Tail72 ft(lane, kg * BN * D);        // (TAIL)
+  f32x4 tail[2] = {zero4(), zero4()};        // (TAIL) dQ^T of queries 0..15 and 16..31
   f32x16 dq[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) dq[db] = zero16();
@@ -393,11 +437,18 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const 
         }
         dp[i] = pv * dp[i];  // P (dP - Delta)
       }
+      bf16x8 dsb[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        const bf16x8 dsb = pack8(dp, t);
+        dsb[t] = pack8(dp, t);
 #pragma unroll
-        for (int db = 0; db < DB; ++db) dq[db] = mfma32(fo.tr8(Kt, kb * 32, t, db), dsb, dq[db]);
+        for (int db = 0; db < DB; ++db) dq[db] = mfma32(fo.tr8(Kt, kb * 32, t, db), dsb[t], dq[db]);
+      }
+      if constexpr (TAIL) {
+        const bf16x8 ktr = ft.read(Kt, kb * 32);
+        tail_operands(dsb[0], dsb[1]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) tail[e] = mfma16(ktr, dsb[e], tail[e]);
       }
     }
   };
@@ -423,7 +474,29 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const 
 
   if constexpr (KG > 1) {
     merge_groups<KG, NWR>(dq, kg, rw, lane, lds);
+    if constexpr (TAIL) {
+      f32x16 all[1] = {zero16()};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) all[0][i] = tail[i / 4][i % 4];
+      __syncthreads();
+      merge_groups<KG, NWR>(all, kg, rw, lane, lds);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) tail[i / 4][i % 4] = all[0][i];
+    }
     if (kg > 0) return;  // no barrier follows
+  }
+  if constexpr (TAIL) {
+    if (lane < 32) {  // columns 64 + 4 (l / 16) + i of queries l % 16 and 16 + l % 16
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int q = q0 + rw * 32 + 16 * e + (lane & 15);
+        if (q >= T) continue;
+        bf16x4 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = to_bf16(tail[e][j] * p.scale);
+        *reinterpret_cast<bf16x4*>(p.dq + bi * p.sdq.b + hi * p.sdq.h + q * p.sdq.t + 64 + 4 * (lane >> 4)) = w;
+      }
+    }
   }
   if (qrow >= T) return;
   bf16_t* row = p.dq + bi * p.sdq.b + hi * p.sdq.h + qrow * p.sdq.t;
@@ -432,7 +505,6 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const 
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int col = db * 32 + 8 * g + 4 * (lane >> 5);
-      if (D % 32 != 0 && col >= D) continue;  // (D = 72)
       bf16x4 w;
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[j] = to_bf16(dq[db][4 * g + j] * p.scale);
@@ -450,7 +522,7 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const 
 template <int D, int NW, int G, int BMK, int BNQ, int VL>
 __global__ __launch_bounds__(64 * NW, 2) void bwd_grad_kernel(BwdParams p, int n_dkdv, int n_qtiles) {
   constexpr int B1 = DkdvLds<D, NW, G, BMK, VL>::BYTES, B2 = DqLds<D, NW, BNQ * G>::BYTES;
-  constexpr int B3 = merge_bytes<G, NW / G, (D + 31) / 32>();
+  constexpr int B3 = merge_bytes<G, NW / G, D / 32>();
   constexpr int B12 = B1 > B2 ? B1 : B2;
   __shared__ __attribute__((aligned(16))) unsigned char lds[B12 > B3 ? B12 : B3];
   const int id = blockIdx.x;

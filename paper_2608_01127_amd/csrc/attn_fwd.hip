@@ -137,7 +137,9 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
   constexpr int BM = 32 * RB * NWR, NT = 64 * NW, KB = BN / 32;
   constexpr int BK = BN * KG;            // keys staged per step
   constexpr int KK = (D + 15) / 16;  // contraction steps over D (D = 72: the last one half zeros)
-  constexpr int DB = (D + 31) / 32;  // 32-wide column blocks of D (D = 72: the last one 8 wide)
+  constexpr int DB = D / 32;         // 32-wide column blocks of D
+  constexpr bool TAIL = D % 32 != 0;  // D = 72: eight columns more (Tail72)
+  static_assert(!TAIL || RB == 1, "one row block with a tail");
   constexpr int TE = stage_elems<D, BK, NT>();  // elements of one staged tile buffer
   __shared__ __attribute__((aligned(16))) bf16_t lds[2][NSTG][TE];  // K, V x stages
   bf16_t(*Ks)[TE] = lds[0];
@@ -198,6 +200,8 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
   };
 
   f32x16 o[RB][DB];
+  f32x4 ot[2] = {zero4(), zero4()};  // (TAIL) O^T of columns 64.., queries 0..15 and 16..31 of the wave
+  const int tq = lane & 15;          // (TAIL) this lane's query in ot[0], and 16 before the one in ot[1]
   float m[RB], lsum[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -222,6 +226,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
   // registers (one add, shared by the key blocks) plus an immediate.  A key
   // group's slice of the staged keys is folded in here.
   const FragOffsets<D> fo(lane, kg * BN * D);
+  const Tail72 ft(lane, kg * BN * D);  // (TAIL)
 
   auto step = [&](auto masked, const int k0, const bf16_t* Kt, const bf16_t* Vt) {
     // S^T for KB 32-key blocks x RB row blocks; each K fragment is read once
@@ -284,6 +289,10 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
 #pragma unroll
           for (int i = 0; i < 16; ++i) o[rb][db][i] *= alpha;
         }
+        if constexpr (TAIL) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) ot[e] *= __shfl(alpha, 16 * e + tq);
+        }
         m[rb] = need[rb] ? mx[rb] : m[rb];
       }
     }
@@ -306,17 +315,25 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
     // O^T += V^T P^T; each V fragment is read once for all row blocks
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
+      bf16x8 pt[2];  // (TAIL)
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         bf16x8 pb[RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) pb[rb] = pack8(s[rb][kb], t);
+        pt[t] = pb[0];
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
           const bf16x8 vfrag = fo.tr8(Vt, kb * 32, t, db);
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb) o[rb][db] = mfma32(vfrag, pb[rb], o[rb][db]);
         }
+      }
+      if constexpr (TAIL) {
+        const bf16x8 vfrag = ft.read(Vt, kb * 32);
+        tail_operands(pt[0], pt[1]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) ot[e] = mfma16(vfrag, pt[e], ot[e]);
       }
     }
   };
@@ -423,9 +440,11 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
     // M = max_g m_g, w_g = 2^(m_g - M), O = sum_g w_g O_g, l = sum_g w_g l_g.
     constexpr int XO = (KG - 1) * NWR * RB * DB * 16 * 64;  // floats of O
     constexpr int XM = (KG - 1) * NWR * RB * 2 * 64;        // floats of (m, l)
-    static_assert((XO + XM) * 4 <= (int)sizeof(lds), "exchange fits the K/V stages");
+    constexpr int XT = TAIL ? (KG - 1) * NWR * 2 * 4 * 64 : 0;
+    static_assert((XO + XM + XT) * 4 <= (int)sizeof(lds), "exchange fits the K/V stages");
     float* xo = reinterpret_cast<float*>(&lds[0][0][0]);
     float* xm = xo + XO;
+    float* xt = xm + XM;
     __syncthreads();
     if (kg > 0) {
 #pragma unroll
@@ -435,6 +454,10 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
         for (int db = 0; db < DB; ++db) {
 #pragma unroll
           for (int i = 0; i < 16; ++i) xo[((slot * DB + db) * 16 + i) * 64 + lane] = o[rb][db][i];
+        }
+        if constexpr (TAIL) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) xt[(slot * 8 + i) * 64 + lane] = ot[i / 4][i % 4];
         }
         xm[(slot * 2) * 64 + lane] = m[rb];
         xm[(slot * 2 + 1) * 64 + lane] = lsum[rb];
@@ -474,6 +497,19 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
           o[rb][db][i] = acc;
         }
       }
+      if constexpr (TAIL) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          ot[e] *= __shfl(wg[0], 16 * e + tq);
+#pragma unroll
+          for (int g = 1; g < KG; ++g) {
+            const int slot = ((g - 1) * NWR + rw) * RB + rb;
+            const float w = __shfl(wg[g], 16 * e + tq);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ot[e][i] += w * xt[(slot * 8 + 4 * e + i) * 64 + lane];
+          }
+        }
+      }
       m[rb] = M;
       lsum[rb] = l;
     }
@@ -482,6 +518,23 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     lsum[rb] = sum_halves(lsum[rb]);
+    if constexpr (TAIL) {  // lanes 0..31: columns 64 + 4 (l / 16) + i of the two queries
+      const float inv = 1.f / lsum[rb];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float iv = __shfl(inv, 16 * e + tq);
+        const int q = q0 + rw * 32 + 16 * e + tq, col = 64 + 4 * (lane >> 4);
+        if (lane >= 32 || q >= p.Tq) continue;
+        if (nst > 1) {
+          *reinterpret_cast<f32x4*>(p.part + (((long long)split * p.BH + bh) * p.split_rows + q) * D + col) = ot[e];
+        } else {
+          bf16x4 w;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) w[j] = to_bf16(ot[e][j] * iv);
+          *reinterpret_cast<bf16x4*>(p.o + b_ * p.so.b + h_ * p.so.h + q * p.so.t + col) = w;
+        }
+      }
+    }
     if (qrow[rb] >= p.Tq) continue;
     if (nst > 1) {
       // partial result of this key range: unnormalised O, the reference max m
@@ -495,7 +548,6 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int col = db * 32 + 8 * g + 4 * (lane >> 5);
-          if (D % 32 != 0 && col >= D) continue;  // (D = 72)
           f32x4 w;
 #pragma unroll
           for (int j = 0; j < 4; ++j) w[j] = o[rb][db][4 * g + j];
@@ -515,7 +567,6 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_fwd_kernel(FwdParams p) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int col = db * 32 + 8 * g + 4 * (lane >> 5);
-          if (D % 32 != 0 && col >= D) continue;  // (D = 72)
           bf16x4 w;
 #pragma unroll
           for (int j = 0; j < 4; ++j) w[j] = to_bf16(o[rb][db][4 * g + j] * inv);

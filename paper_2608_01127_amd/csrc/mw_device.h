@@ -72,9 +72,9 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& c, int t) {
 //
 // D = 72 (nine slots, not a power of two) keeps rows dense and unswizzled:
 // rows 144 bytes (36 banks) apart already put 16 consecutive rows on disjoint
-// banks.  Its MFMA steps run over 80 (QK^T) and 96 (PV) columns; the columns
-// past 72 read the next row (or the slack after the tile) and meet zeros in
-// the register operand or land in output columns that are never stored.
+// banks.  Its QK^T steps run over 80 columns, whose last eight read the next row
+// (or the slack after the tile) and meet zeros in the register operand; its
+// output columns are two blocks of 32 and a tail of eight (Tail72).
 template <int D>
 struct Tile {
   static_assert(D == 64 || D == 72 || D == 128, "head dimension");
@@ -135,7 +135,7 @@ __device__ __forceinline__ bf16x8 lds_tr8(const bf16_t* tile, int rbase, int t, 
 // a constant offset that the compiler folds into the instruction.
 template <int D>
 struct FragOffsets {
-  static constexpr int KK = (D + 15) / 16, DB = (D + 31) / 32;
+  static constexpr int KK = (D + 15) / 16, DB = D / 32;
   int row[KK], tr[DB][2];
   __device__ __forceinline__ FragOffsets(int lane, int extra) {
 #pragma unroll
@@ -176,6 +176,52 @@ template <int D>
 __device__ __forceinline__ bf16x8 FragOffsets<D>::tr8(const bf16_t* tile, int rbase, int t, int db) const {
   return lds_tr8_at(tile + tr[db][0] + (rbase + 16 * t) * D, tile + tr[db][1] + (rbase + 16 * t) * D);
 }
+
+// D = 72: the output columns 64..71, which a third 32-column block would pad to
+// 96.  They take v_mfma_f32_16x16x32_bf16 instead, one per 16 columns of the
+// accumulator's lane axis, over 32 contraction rows (half the matrix time of the
+// padded block, 8 accumulator registers for 16):
+//   D[16x16] += A[16x32] B[32x16]
+//     A: lane l holds A[m = l%16][k = 8*(l/16) + j]; B: B[k = 8*(l/16) + j][n = l%16]
+//     C/D: lane l, register i holds C[m = 4*(l/16) + i][n = l%16]
+// The B operands come from the two packed halves of a 32 x 32 accumulator tile
+// (pack8 of t = 0 and 1): exchanging 16-lane rows between them leaves lane group
+// g = l/16 with the slots of half-wave g/2 and step t = g%2, of columns 0..15 in
+// the first and 16..31 in the second.  The A operand follows that order: lane
+// group g reads rows row(g%2, 8*(g/2) + j) of the LDS tile, columns 64..79 (the
+// last eight, the next row's, give output rows that are never stored).  Against
+// a padded third block, 16 heads x 19200: backward 3194 -> 3012 us (matrix work
+// 22 -> 20 of 32 cycles per block in dK/dV, 16 -> 15 in dQ), forward 1026 -> 996
+// (bound by its softmax VALU work, which stays).
+struct Tail72 {
+  int off[2];
+  __device__ __forceinline__ Tail72(int lane, int extra) {
+    const int g = lane >> 4, a = lane & 15;
+    const int row = 16 * (g & 1) + 4 * (g >> 1) + (a >> 2);
+    off[0] = Tile<72>::off(row, 64 + 4 * (a & 3)) + extra;
+    off[1] = off[0] + 8 * 72;
+  }
+  // A operand for the contraction rows rbase .. rbase + 31 of `tile`
+  __device__ __forceinline__ bf16x8 read(const bf16_t* tile, int rbase) const {
+    return lds_tr8_at(tile + off[0] + rbase * 72, tile + off[1] + rbase * 72);
+  }
+};
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// The packed halves b0, b1 of an accumulator tile -> the two B operands above.
+__device__ __forceinline__ void tail_operands(bf16x8& b0, bf16x8& b1) {
+  u32x4 x = __builtin_bit_cast(u32x4, b0), y = __builtin_bit_cast(u32x4, b1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x[i], y[i], false, false);
+    x[i] = r[0];
+    y[i] = r[1];
+  }
+  b0 = __builtin_bit_cast(bf16x8, x);
+  b1 = __builtin_bit_cast(bf16x8, y);
+}
+__device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 
 // ---------------------------------------------------------------------------
 // Direct global -> LDS staging (global_load_lds_dwordx4): each lane's 16 bytes
