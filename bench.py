@@ -671,7 +671,7 @@ def main():
     bwd_digest = source_digest(["paper_2608_01127_amd/csrc/attn_bwd.hip", "paper_2608_01127_amd/csrc/mw_device.h",
                                 "paper_2608_01127_amd/csrc/mw_kernels.h", "paper_2608_01127_amd/build.py"])
     roofline = {"kernel": "mw_block_causal_attn_bwd at B1 H16 T42240 D128 L2640 = bwd_rowterms_kernel<128> + "
-                          "bwd_grad_kernel<128, 4, 1, 32, 64, 6>",
+                          "bwd_grad_kernel<128, 4, 1, 32, 64, 6, 2>",
                 "bound": "mfma", "achieved": round(tfl(t128.F_bwd, ph["bwd_d128"]), 2), "peak": PEAK_BF16_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(tfl(t128.F_bwd, ph["bwd_d128"]) / PEAK_BF16_TFLOPS, 4),
                 "traffic": read_traffic("train_bwd_d128", bwd_digest),

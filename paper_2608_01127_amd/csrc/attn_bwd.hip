@@ -119,7 +119,7 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const int bh, cons
   constexpr int NWK = NW / QG, BN = 32 * NWK, NT = 64 * NW;
   static_assert(BM % 32 == 0, "32-row query blocks");
   constexpr int KK = (D + 15) / 16, DB = D / 32;  // D = 72: 80 columns, and a tail of 8 (Tail72)
-  static_assert(VL == 0 || (D % 16 == 0 && VL <= KK), "the V fragments in LDS have no zero columns past D");
+  static_assert(16 * VL <= D, "the V fragments in LDS have no zero columns past D");
   using LD = DkdvLds<D, NW, QG, BM, VL>;
   constexpr int TE = LD::TE, RT = LD::RT, BS = LD::BS;
   bf16_t(*Qs)[TE] = reinterpret_cast<bf16_t(*)[TE]>(lds);
@@ -513,14 +513,15 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const 
   }
 }
 
-// dK/dV and dQ work in one grid (both run two waves per SIMD): the first n_dkdv workgroups take key tiles, the rest query
-// tiles, so the query tiles fill the CUs that the key tiles' tail leaves idle
-// and no kernel boundary separates them.  Each part keeps its own XCD-aware,
-// heaviest-first order (tile_item: n_dkdv is a multiple of its head groups, so
-// the dQ part's groups are the dK/dV part's).  Early keys are seen by the most queries and late queries see the
-// most keys: both parts run their heaviest tiles first.
-template <int D, int NW, int G, int BMK, int BNQ, int VL>
-__global__ __launch_bounds__(64 * NW, 2) void bwd_grad_kernel(BwdParams p, int n_dkdv, int n_qtiles) {
+// dK/dV and dQ work in one grid: the first n_dkdv workgroups take key tiles,
+// the rest query tiles, so the query tiles fill the CUs that the key tiles' tail
+// leaves idle and no kernel boundary separates them.  Each part keeps its own
+// XCD-aware, heaviest-first order (tile_item: n_dkdv is a multiple of its head
+// groups, so the dQ part's groups are the dK/dV part's).  Early keys are seen by
+// the most queries and late queries see the most keys: both parts run their
+// heaviest tiles first.
+template <int D, int NW, int G, int BMK, int BNQ, int VL, int WPS>
+__global__ __launch_bounds__(64 * NW, WPS) void bwd_grad_kernel(BwdParams p, int n_dkdv, int n_qtiles) {
   constexpr int B1 = DkdvLds<D, NW, G, BMK, VL>::BYTES, B2 = DqLds<D, NW, BNQ * G>::BYTES;
   constexpr int B3 = merge_bytes<G, NW / G, D / 32>();
   constexpr int B12 = B1 > B2 ? B1 : B2;
@@ -537,10 +538,11 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_grad_kernel(BwdParams p, int n
 }
 
 // Configurations of the gradient grid: NW waves in G query (dK/dV) or key (dQ)
-// groups, BMK queries and BNQ keys per group and step.
-template <int NW_, int G_, int BMK_, int BNQ_, int VL_>
+// groups, BMK queries and BNQ keys per group and step, registers for WPS waves
+// per SIMD.
+template <int NW_, int G_, int BMK_, int BNQ_, int VL_, int WPS_>
 struct BwdTile {
-  static constexpr int NW = NW_, G = G_, BMK = BMK_, BNQ = BNQ_, VL = VL_;
+  static constexpr int NW = NW_, G = G_, BMK = BMK_, BNQ = BNQ_, VL = VL_, WPS = WPS_;
   static constexpr int ROWS = 32 * (NW / G);  // keys (dK/dV) and queries (dQ) per workgroup
 };
 // 128 keys or queries.  D = 128: V fragments in LDS and 32-query steps bring the
@@ -551,14 +553,19 @@ struct BwdTile {
 // 5% fewer LDS reads, 16 heads x 42240 23.25 -> 23.14 ms, x 9600 1272 -> 1264 us
 // against all eight in LDS.
 template <int D>
-using Wide = BwdTile<4, 1, D == 128 ? 32 : 64, D == 64 ? 128 : 64, D == 128 ? 6 : 0>;
+using Wide = BwdTile<4, 1, D == 128 ? 32 : 64, D == 64 ? 128 : 64, D == 128 ? 6 : 0, 2>;
+// D = 64, grids of more than 900 64-row tiles: 64-key dQ steps halve the LDS, and
+// 168 registers let three waves run per SIMD.  (Wide | Wide3), us: 24 heads x
+// 10560 1268 | 1247, 16 x 5000 215 | 209, 24 x 2600 105 | 103; below, where a third
+// workgroup per CU only adds to the longest chain: 16 x 3200 94 | 100.
+using Wide3 = BwdTile<4, 1, 64, 64, 0, 3>;
 // 64 keys or queries, two groups of two waves: half the chain.  (D = 128: with
 // one V fragment in registers two workgroups fit a CU's LDS; with none, one.)
 template <int D>
-using Pairs = BwdTile<4, 2, 32, 32, D == 128 ? 7 : 0>;
+using Pairs = BwdTile<4, 2, 32, 32, D == 128 ? 7 : 0, 2>;
 // 64 keys or queries, four groups of two waves: a quarter of the chain.
 template <int D>
-using Quads = BwdTile<8, 4, 32, 32, D == 128 ? 8 : 0>;
+using Quads = BwdTile<8, 4, 32, 32, D == 128 ? 8 : 0, 2>;
 
 // Small grids are bound by the chain of steps one wave walks (about 1.3 us a
 // step), so they split it; the price is staging Q and dO (K and V) for half the
@@ -571,8 +578,7 @@ using Quads = BwdTile<8, 4, 32, 32, D == 128 ? 8 : 0>;
 //   16 x 2400 (69 | 71 | 89); D = 72: 12 x 600 (22 | 17 | 18), 4 x 8872 (248 | 221 |
 //   241), 16 x 2400 (89 | 92 | 112).
 template <int D>
-static int wave_groups(int BH, int T) {
-  const long long tiles = (long long)BH * ((T + 63) / 64);
+static int wave_groups(long long tiles, int T) {
   if (tiles <= 128 && T >= (D == 128 ? 512 : 768)) return 4;
   if (tiles <= 320 && T >= 4096) return 4;
   return tiles <= 576 ? 2 : 1;
@@ -581,7 +587,7 @@ static int wave_groups(int BH, int T) {
 template <int D, class C>
 static hipError_t launch_grad(const BwdParams& p, hipStream_t stream) {
   const int n = (p.T + C::ROWS - 1) / C::ROWS;
-  hipLaunchKernelGGL((bwd_grad_kernel<D, C::NW, C::G, C::BMK, C::BNQ, C::VL>), dim3(2 * n * p.BH), dim3(64 * C::NW),
+  hipLaunchKernelGGL((bwd_grad_kernel<D, C::NW, C::G, C::BMK, C::BNQ, C::VL, C::WPS>), dim3(2 * n * p.BH), dim3(64 * C::NW),
                      0, stream, p, n * p.BH, n);
   return hipGetLastError();
 }
@@ -594,8 +600,12 @@ static hipError_t launch_bwd_d(const BwdParams& p, hipStream_t stream) {
                      rows);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int groups = wave_groups<D>(p.BH, p.T);
+  const long long tiles = (long long)p.BH * ((p.T + 63) / 64);
+  const int groups = wave_groups<D>(tiles, p.T);
   if (groups == 4) return launch_grad<D, Quads<D>>(p, stream);
+  if constexpr (D == 64) {
+    if (tiles > 900) return launch_grad<D, Wide3>(p, stream);
+  }
   return groups == 2 ? launch_grad<D, Pairs<D>>(p, stream) : launch_grad<D, Wide<D>>(p, stream);
 }
 
