@@ -735,7 +735,9 @@ static FwdChoice cached_choice(int fallback, int stream_wgs) {
 #define MW_CAT_(a, b) a##b
 #define MW_CAT(a, b) MW_CAT_(a, b)
 constexpr int kD = MW_FWD_HEAD_DIM;
-// Cached calls of more than 64 rows: 128-row tiles, except long queues at D = 64
+// Cached calls of more than 64 rows: 128-row tiles, except beyond 256 rows at D =
+// 64 (72 heads x 400 rows over 2 x 300 tokens: 27.5 us in 256-row tiles, 30.0 in
+// 128-row ones; 48 x 226 over 3 x 880: 28.6 | 25.9)
 using CachedLong = std::conditional_t<kD == 64, Rows256x2, Rows128<kD>>;
 hipError_t MW_CAT(launch_fwd_, MW_FWD_HEAD_DIM)(const FwdParams& p, bool cached, hipStream_t stream) {
   const GridFill fill = cached ? unsplit_fill(kD, p.BH, p.Tk) : grid_fill(kD, p.BH, p.Tk);
@@ -747,14 +749,16 @@ hipError_t MW_CAT(launch_fwd_, MW_FWD_HEAD_DIM)(const FwdParams& p, bool cached,
   if (p.Tq <= 64) return launch_tile<kD, true, Stream64>(p, stream);
   if (p.n_splits <= 1 && fill == GridFill::sparse) return launch_tile<kD, true, Rows64x8>(p, stream);
   if (p.n_splits <= 1 && fill == GridFill::small) return launch_tile<kD, true, Rows64<kD>>(p, stream);
-  if (p.Tq <= 512) return launch_tile<kD, true, Rows128<kD>>(p, stream);
+  if (p.Tq <= 256) return launch_tile<kD, true, Rows128<kD>>(p, stream);
   return launch_tile<kD, true, CachedLong>(p, stream);
 }
 // (fallbacks, as built: Stream64 holds 64 KB of LDS at D = 64 and 96 KB at 72)
 FwdChoice MW_CAT(fwd_choice_, MW_FWD_HEAD_DIM)(int Tq) {
   if (Tq <= 64) return cached_choice<kD, Stream64>(kD == 64 ? 2 : 1, 1);
-  if (Tq <= 512) return cached_choice<kD, Rows128<kD>>(3, 3);
-  return cached_choice<kD, CachedLong>(kD == 64 ? 2 : 3, kD == 64 ? 1 : 3);
+  // (two streaming workgroups a CU: 48 heads x 226 rows over 3 x 880, D = 72, us
+  // with three | two | one: 31.5 | 27.6 | 35.6)
+  if (Tq <= 256) return cached_choice<kD, Rows128<kD>>(3, 2);
+  return cached_choice<kD, CachedLong>(kD == 64 ? 2 : 3, kD == 64 ? 1 : 2);
 }
 #elif !defined(MW_FWD_DECODE) && !defined(MW_FWD_CACHED) && !defined(MW_FWD_SMALL)
 hipError_t launch_fwd_128(const FwdParams& p, bool cached, hipStream_t stream) {

@@ -10,7 +10,7 @@ from test_abi_host import new_cache
 
 @pytest.mark.parametrize("H,D,q_len,bm,per_cu", [(12, 128, 64, 64, 1), (24, 128, 64, 64, 1), (24, 128, 100, 128, 1),
                                                  (36, 128, 33, 64, 1), (40, 64, 64, 64, 1), (24, 72, 17, 64, 1),
-                                                 (24, 72, 100, 128, 3), (20, 64, 128, 128, 3), (72, 128, 94, 128, 1)])
+                                                 (24, 72, 100, 128, 2), (20, 64, 128, 128, 2), (72, 128, 94, 128, 1)])
 def test_streaming_splits_fill_rounds(H, D, q_len, bm, per_cu):
     lib = mw.load()
     c = new_cache(S=8, B=1, H=H, L=2640, D=D)
