@@ -516,10 +516,9 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const int bh, const 
 // dK/dV and dQ work in one grid: the first n_dkdv workgroups take key tiles,
 // the rest query tiles, so the query tiles fill the CUs that the key tiles' tail
 // leaves idle and no kernel boundary separates them.  Each part keeps its own
-// XCD-aware, heaviest-first order (tile_item: n_dkdv is a multiple of its head
-// groups, so the dQ part's groups are the dK/dV part's).  Early keys are seen by
-// the most queries and late queries see the most keys: both parts run their
-// heaviest tiles first.
+// XCD-aware, heaviest-first order (tile_item).  Early keys are seen by the most
+// queries and late queries see the most keys: both parts run their heaviest tiles
+// first.
 template <int D, int NW, int G, int BMK, int BNQ, int VL, int WPS>
 __global__ __launch_bounds__(64 * NW, WPS) void bwd_grad_kernel(BwdParams p, int n_dkdv, int n_qtiles) {
   constexpr int B1 = DkdvLds<D, NW, G, BMK, VL>::BYTES, B2 = DqLds<D, NW, BNQ * G>::BYTES;
@@ -527,12 +526,12 @@ __global__ __launch_bounds__(64 * NW, WPS) void bwd_grad_kernel(BwdParams p, int
   constexpr int B12 = B1 > B2 ? B1 : B2;
   __shared__ __attribute__((aligned(16))) unsigned char lds[B12 > B3 ? B12 : B3];
   const int id = blockIdx.x;
-  int bh, r, split;
+  int bh, r;
   if (id < n_dkdv) {
-    tile_item(id, p.BH, 1, bh, r, split);
+    tile_item(id, p.BH, bh, r);
     dkdv_body<D, NW, G, BMK, VL>(p, bh, r, lds);
   } else {
-    tile_item(id - n_dkdv, p.BH, 1, bh, r, split);
+    tile_item(id - n_dkdv, p.BH, bh, r);
     dq_body<D, NW, G, BNQ>(p, bh, n_qtiles - 1 - r, lds);
   }
 }

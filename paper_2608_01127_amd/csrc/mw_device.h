@@ -427,29 +427,26 @@ __device__ __forceinline__ int xcd_remap(int bid, int n) {
   return (bid % 8) * (n / 8) + bid / 8;
 }
 
-// Work order of the training grids.  Workgroup `bid` of n = BH * ntiles * NS
-// gets (batch*head, tile rank, key range), rank 0 being the heaviest tile of its head.
-// Workgroup ids are dealt to the 8 XCDs round-robin.  With g the largest power
-// of two up to 8 that divides BH, the XCDs x with the same x mod g share BH / g
-// whole heads, so that a head's K/V stay in 8 / g L2s, and take their tiles
-// heaviest first across those heads.  (n mod 8 is a multiple of g, so the last,
-// partial row of workgroup ids gives every group the same number.)
-// Against taking the heads one after another, whose last heads' heavy tiles
-// start late: 12 heads x 19200 tokens (D = 128, g = 4) forward 1226 -> 1048 us
-// and backward 4063 -> 3620, 15 heads x 2999 (D = 72, g = 1) backward 121 -> 104;
-// at g = 8 a simulation of the D = 64 training shape's dispatch gives a 23%
-// shorter makespan.
-// With NS key ranges per tile (1 in training) a tile's ranges are neighbours.
-// (The 256-row D = 128 forward, whose loop the scheduler lays out anew with every
-// change around it, measured 1% faster with NS kept general than fixed to 1.)
-__device__ __forceinline__ void tile_item(int bid, int BH, int NS, int& bh, int& rank, int& split) {
-  const int low = BH & -BH, g = low < 8 ? low : 8;  // 1, 2, 4 or 8
-  const int x = bid % 8, group = x & (g - 1), hpg = BH / g;
-  const int j = (bid / 8) * (8 / g) + x / g;  // the group's j-th workgroup
-  const int r = j / (hpg * NS), rem = j - r * (hpg * NS);
-  bh = group * hpg + rem / NS;
-  rank = r;
-  split = rem % NS;
+// Work order of the training grids: (batch*head, tile rank) of workgroup `bid` of
+// BH * ntiles, rank 0 being the heaviest tile of its head.  All heads' tiles of one
+// rank come before the next rank's, so the heaviest start first and the lightest
+// end the grid.  Workgroup ids are dealt to the 8 XCDs round-robin: within a rank
+// the last 8 k heads are placed so that each always meets the same XCD, whose L2
+// then holds its K/V alone; the first BH % 8 (= n) heads, with g the largest power
+// of two that divides n, are each spread over 8 / g XCDs.
+// Against taking the heads one after another, whose last heads' heavy tiles start
+// late: 12 heads x 19200 tokens (D = 128) forward 1226 -> 1034 us, 15 heads x 2999
+// (D = 72) backward 121 -> 104; at BH % 8 = 0 a simulation of the D = 64 training
+// shape's dispatch gives a 23% shorter makespan.
+// Against spreading every head of an odd count over all XCDs, whose L2s then
+// stream every head's K/V: forward, D = 72, [B, T, H, D] views, 45 heads x 19200
+// 5502 -> 3642 us (one after another 4340), 99 x 3000 329 -> 205 (306).
+__host__ __device__ __forceinline__ void tile_item(int bid, int BH, int& bh, int& rank) {
+  rank = bid / BH;
+  const int p = bid - rank * BH, lead = BH % 8;
+  const int first = p < lead ? 0 : lead, n = p < lead ? lead : BH - lead;
+  const int low = n & -n, g = low < 8 ? low : 8;  // 1, 2, 4 or 8
+  bh = first + (bid & (g - 1)) * (n / g) + (p - first) / g;
 }
 
 // Cached attention: the heads one after another on each XCD (xcd_remap).

@@ -192,6 +192,8 @@ inline long long fwd_prepare(FwdParams& p, int bm, bool cached) {
   p.split_rows = fwd_split_rows(bm, p.Tq, SplitPlan{p.n_splits, p.n_whole});
   return (long long)p.BH * (p.n_whole + (long long)(p.n_qtiles - p.n_whole) * p.n_splits);
 }
+// The training grids' work order (tile_item of mw_device.h), for the host tests.
+void training_work_item(int bid, int BH, int& bh, int& rank);
 hipError_t launch_bwd_64(const BwdParams& p, hipStream_t stream);
 hipError_t launch_bwd_72(const BwdParams& p, hipStream_t stream);
 hipError_t launch_bwd_128(const BwdParams& p, hipStream_t stream);

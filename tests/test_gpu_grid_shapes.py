@@ -23,11 +23,12 @@ def check(mw, B, H, T, D, L):
         assert_close(n, to_f64(g[n]), ref)
 
 
-# Batch x heads of every residue class of the work order (1, 2, 4 or 8 groups of XCDs), with tile
-# counts that leave a partial last row of workgroup ids
+# Batch x heads with and without a multiple of eight heads, every remainder class (spread over 1, 2
+# or 4 groups of XCDs), and tile counts that leave a partial last row of workgroup ids
 @pytest.mark.parametrize("B,H,T,D,L", [(1, 1, 900, 128, 200), (1, 3, 500, 64, 100), (3, 5, 300, 72, 77),
                                        (2, 3, 650, 128, 130), (1, 10, 200, 64, 64), (1, 12, 300, 128, 100),
-                                       (2, 10, 150, 72, 50), (1, 24, 140, 64, 30)])
+                                       (2, 10, 150, 72, 50), (1, 24, 140, 64, 30), (1, 9, 300, 64, 77),
+                                       (1, 13, 150, 72, 50), (2, 7, 200, 128, 100)])
 def test_work_order(mw, B, H, T, D, L):
     check(mw, B, H, T, D, L)
 
