@@ -553,10 +553,8 @@ struct BwdTile {
 // against all eight in LDS.
 template <int D>
 using Wide = BwdTile<4, 1, D == 128 ? 32 : 64, D == 64 ? 128 : 64, D == 128 ? 6 : 0, 2>;
-// D = 64, grids of more than 900 64-row tiles: 64-key dQ steps halve the LDS, and
-// 168 registers let three waves run per SIMD.  (Wide | Wide3), us: 24 heads x
-// 10560 1268 | 1247, 16 x 5000 215 | 209, 24 x 2600 105 | 103; below, where a third
-// workgroup per CU only adds to the longest chain: 16 x 3200 94 | 100.
+// 128 keys or queries, D = 64: 64-key dQ steps halve the LDS, and 168 registers let
+// three waves run per SIMD.
 using Wide3 = BwdTile<4, 1, 64, 64, 0, 3>;
 // 64 keys or queries, two groups of two waves: half the chain.  (D = 128: with
 // one V fragment in registers two workgroups fit a CU's LDS; with none, one.)
@@ -565,23 +563,6 @@ using Pairs = BwdTile<4, 2, 32, 32, D == 128 ? 7 : 0, 2>;
 // 64 keys or queries, four groups of two waves: a quarter of the chain.
 template <int D>
 using Quads = BwdTile<8, 4, 32, 32, D == 128 ? 8 : 0, 2>;
-
-// Small grids are bound by the chain of steps one wave walks (about 1.3 us a
-// step), so they split it; the price is staging Q and dO (K and V) for half the
-// keys (queries), and the merge.  Counted in 64-row tiles over all heads, us as
-// (Wide | Pairs | Quads), backward with its row terms:
-//   D = 128: 1 x 8000 (316 | 182 | 126), 12 x 600 (35 | 25 | 24), 2 x 256
-//   (20 | 14 | 16), 12 x 1200 (61 | 43 | 44), 1 x 20000 (769 | 500 | 421), 8 x 3000
-//   (136 | 98 | 112), 12 x 2400 (118 | 99 | 118), 24 x 2000 (133 | 136 | 168);
-//   D = 64: 4 x 2000 (45 | 32 | 26), 12 x 600 (20 | 15 | 15), 8 x 3000 (69 | 56 | 66),
-//   16 x 2400 (69 | 71 | 89); D = 72: 12 x 600 (22 | 17 | 18), 4 x 8872 (248 | 221 |
-//   241), 16 x 2400 (89 | 92 | 112).
-template <int D>
-static int wave_groups(long long tiles, int T) {
-  if (tiles <= 128 && T >= (D == 128 ? 512 : 768)) return 4;
-  if (tiles <= 320 && T >= 4096) return 4;
-  return tiles <= 576 ? 2 : 1;
-}
 
 template <int D, class C>
 static hipError_t launch_grad(const BwdParams& p, hipStream_t stream) {
@@ -599,14 +580,18 @@ static hipError_t launch_bwd_d(const BwdParams& p, hipStream_t stream) {
                      rows);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const long long tiles = (long long)p.BH * ((p.T + 63) / 64);
-  const int groups = wave_groups<D>(tiles, p.T);
-  if (groups == 4) return launch_grad<D, Quads<D>>(p, stream);
+  const BwdGrid grid = bwd_grid(D, p.BH, p.T);
+  if (grid == BwdGrid::quads) return launch_grad<D, Quads<D>>(p, stream);
+  if (grid == BwdGrid::pairs) return launch_grad<D, Pairs<D>>(p, stream);
   if constexpr (D == 64) {
-    if (tiles > 900) return launch_grad<D, Wide3>(p, stream);
+    if (grid == BwdGrid::wide3) return launch_grad<D, Wide3>(p, stream);
   }
-  return groups == 2 ? launch_grad<D, Pairs<D>>(p, stream) : launch_grad<D, Wide<D>>(p, stream);
+  return launch_grad<D, Wide<D>>(p, stream);
 }
+
+#if MW_BWD_HEAD_DIM == 128
+int training_bwd_grid(int D, int BH, int T) { return (int)bwd_grid(D, BH, T); }
+#endif
 
 // This file is compiled once per head dimension (MW_BWD_HEAD_DIM = 64, 72 or 128):
 // the two instantiations get different instruction-scheduling options in the

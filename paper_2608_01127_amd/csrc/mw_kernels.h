@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+
 namespace mw {
 
 // Element strides of a [B, H, T, D] tensor view (D contiguous): element
@@ -192,7 +195,43 @@ inline long long fwd_prepare(FwdParams& p, int bm, bool cached) {
   p.split_rows = fwd_split_rows(bm, p.Tq, SplitPlan{p.n_splits, p.n_whole});
   return (long long)p.BH * (p.n_whole + (long long)(p.n_qtiles - p.n_whole) * p.n_splits);
 }
-// The training grids' work order (tile_item of mw_device.h), for the host tests.
+// Configuration of the gradient grid (attn_bwd.hip), by the 64-row tiles of the
+// sequence over all heads and its length.  A wave walks about T / 64 steps of
+// 1.3 us; a small grid is bound by that chain, so two or four wave groups split
+// it, for the price of staging Q and dO (K and V) for half the keys (queries), and
+// the merge.  Backward with its row terms, us, as (128 rows | 64 in two groups |
+// 64 in four), on both sides of each line:
+//   four groups: the longer the chain, the more tiles; a short one does not repay
+//   the merge (D = 64: 4 x 512 +4% against two, 4 x 768 -1%; D = 128: 4 x 400 +7%,
+//   4 x 512 -1%).  D = 64: 2 x 1024 (29 | 21 | 18),
+//   12 x 1024 (- | 31 | 34), 4 x 2500 (55 | 39 | 31), 8 x 2048 (- | 40 | 44),
+//   4 x 4096 (81 | 58 | 53), 5 x 4096 (84 | 62 | 69), 1 x 24000 (435 | 304 | 283),
+//   1 x 30000 (564 | 405 | 444); D = 72: 9 x 1024 +3%, 5 x 2500 -3%, 3 x 6800 +2%
+//   against two; D = 128: 12 x 1024 +7%, 8 x 1500 -2%, 6 x 3000 -1%, 3 x 8000
+//   (310 | 210 | 216), 2 x 12000 (450 | 303 | 283), 2 x 16000 (618 | 429 | 475);
+//   two groups: up to about one round of 128-row workgroups (512 to 576 64-row
+//   tiles), fewer where the sequence is short and every tile of much the same
+//   weight.  D = 64: 46 x 512 (360 tiles) -6%, 60 x 512 -1%, 68 x 512 +13%; 32 x
+//   1000 (32 | 29), 36 x 1000 +9%; 18 x 2000 -2%, 20 x 2000 +2%; D = 72: 36 x 700
+//   -1%, 40 x 700 +2%, 23 x 1500 -5%, 24 x 1500 (64 | 67); D = 128: 64 x 512 -5%, 68
+//   x 512 +8%, 67 x 330 -2%, 80 x 330 +5%;
+//   wide3 (D = 64; three waves per SIMD) where a third workgroup per CU does not
+//   only add to the longest chain, us as (wide | wide3): 8 x 7200 (191 | 215), 1 x
+//   60000 (1382 | 1639), 12 x 5120 (153 | 164), 4 x 18000 (563 | 591), 6 x 13000
+//   (473 | 452), 8 x 12000 (527 | 510), 24 x 10560 (1268 | 1247), and with short
+//   chains 24 x 2500 (103 | 96), 48 x 1280 (68 | 61), 20 x 3200 (116 | 115).
+enum class BwdGrid { wide = 0, pairs = 2, wide3 = 3, quads = 4 };
+inline BwdGrid bwd_grid(int D, int BH, int T) {
+  const long long tiles = (long long)BH * ((T + 63) / 64);
+  const double chain = std::log2((double)T) - 8;
+  if (T >= (D == 128 ? 512 : 768) && tiles <= (D == 128 ? 75 * chain : std::min(440., 70 * chain))) return BwdGrid::quads;
+  if (tiles <= (D == 128 ? std::min(576, 256 + T / 2) : std::min({576, 272 + T / 4, 480 + T / 20}))) return BwdGrid::pairs;
+  if (D == 64 && (tiles > 1130 || (tiles > 900 && T <= 3200))) return BwdGrid::wide3;
+  return BwdGrid::wide;
+}
+// The training grids' configuration and work order (tile_item of mw_device.h), for
+// the host tests.
+int training_bwd_grid(int D, int BH, int T);
 void training_work_item(int bid, int BH, int& bh, int& rank);
 hipError_t launch_bwd_64(const BwdParams& p, hipStream_t stream);
 hipError_t launch_bwd_72(const BwdParams& p, hipStream_t stream);

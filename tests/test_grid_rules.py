@@ -1,0 +1,44 @@
+"""Which configuration a training grid takes (host side, no GPU): the measured points on both sides
+of each line, and that the GPU tests reach every configuration."""
+import ctypes
+
+import pytest
+
+import paper_2608_01127_amd as mw
+import test_gpu_grid_shapes as shapes
+
+WIDE, PAIRS, WIDE3, QUADS = 0, 2, 3, 4
+
+
+def bwd_grid(D, BH, T):
+    fn = mw.load()["_ZN2mw17training_bwd_gridEiii"]  # mw::training_bwd_grid(int, int, int)
+    fn.restype, fn.argtypes = ctypes.c_int, [ctypes.c_int] * 3
+    return fn(D, BH, T)
+
+
+# (heads, tokens) where one configuration measured at least 4% ahead of the next
+@pytest.mark.parametrize("D,BH,T,grid", [
+    # short sequences in one round of 128-row tiles: two groups lose
+    (64, 65, 512, WIDE), (64, 80, 330, WIDE), (72, 93, 330, WIDE), (72, 120, 200, WIDE), (128, 120, 200, WIDE),
+    (128, 93, 330, WIDE), (128, 68, 512, WIDE), (64, 40, 512, PAIRS), (72, 40, 512, PAIRS), (128, 60, 512, PAIRS),
+    (64, 12, 2400, PAIRS), (64, 32, 1000, PAIRS), (72, 24, 1500, WIDE), (128, 18, 2000, PAIRS), (72, 8, 4096, PAIRS),
+    # four groups
+    (64, 5, 4096, PAIRS), (72, 5, 4096, PAIRS), (64, 4, 5000, PAIRS), (64, 12, 1024, PAIRS), (128, 12, 1024, PAIRS),
+    (64, 1, 24000, QUADS), (128, 1, 24000, QUADS), (64, 4, 2500, QUADS), (64, 8, 1000, QUADS), (128, 4, 4096, QUADS), (128, 2, 12000, QUADS),
+    (64, 1, 30000, PAIRS), (128, 2, 16000, PAIRS), (64, 2, 256, PAIRS), (128, 1, 400, PAIRS), (72, 8, 512, PAIRS),
+    # three waves per SIMD
+    (64, 8, 7200, WIDE), (64, 1, 60000, WIDE), (64, 12, 5120, WIDE), (64, 4, 18000, WIDE), (64, 6, 13000, WIDE3),
+    (64, 24, 2500, WIDE3), (64, 48, 1280, WIDE3), (64, 24, 10560, WIDE3)])
+def test_backward_lines(D, BH, T, grid):
+    assert bwd_grid(D, BH, T) == grid
+
+
+def gpu_shapes():
+    for fn in (shapes.test_work_order, shapes.test_forward_tiles):
+        for B, H, T, D, _ in fn.pytestmark[0].args[1]:
+            yield D, B * H, T
+
+
+def test_gpu_shapes_reach_every_configuration():
+    reached = {(D, bwd_grid(D, BH, T)) for D, BH, T in gpu_shapes()}
+    assert reached == {(D, g) for D in (64, 72, 128) for g in (WIDE, PAIRS, QUADS)} | {(64, WIDE3)}
