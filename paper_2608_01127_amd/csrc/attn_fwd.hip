@@ -594,7 +594,8 @@ struct FwdTile {
   static constexpr int BK = BN * KG;              // keys per step
 };
 // 256 rows.  D = 128: eight waves share each staged K/V tile (240 registers,
-// one workgroup per CU).  D = 64 (cached calls): four waves of two row blocks.
+// one workgroup per CU).  D = 64 (large training grids, long cached queues): four
+// waves of two row blocks.
 using Rows256 = FwdTile<8, 64, 1, 1, 2, 1>;
 using Rows256x2 = FwdTile<4, 64, 2, 1, 2, 2>;
 // 128 rows, four waves.  D = 64 and 72 at three waves per SIMD (<= 168
@@ -748,6 +749,9 @@ hipError_t MW_CAT(launch_fwd_, MW_FWD_HEAD_DIM)(const FwdParams& p, bool cached,
   if (!cached) {
     if (fill == GridFill::sparse) return launch_tile<kD, false, Rows64x8>(p, stream);
     if (fill == GridFill::small) return launch_tile<kD, false, Rows64<kD>>(p, stream);
+    if constexpr (kD == 64) {
+      if (fill == GridFill::large) return launch_tile<kD, false, Rows256x2>(p, stream);
+    }
     return launch_tile<kD, false, Rows128<kD>>(p, stream);
   }
   if (p.Tq <= 64) return launch_tile<kD, true, Stream64>(p, stream);
@@ -807,6 +811,7 @@ FwdChoice fwd_choice(int D, int Tq) {
   return Tq <= 512 ? fwd_choice_decode_128(Tq) : fwd_choice_cached_128();
 }
 
+int training_fwd_fill(int D, int BH, int T) { return (int)grid_fill(D, BH, T); }
 void training_work_item(int bid, int BH, int& bh, int& rank) { tile_item(bid, BH, bh, rank); }
 
 hipError_t launch_combine(const FwdParams& p, int D, hipStream_t stream) {

@@ -133,14 +133,19 @@ FwdChoice fwd_choice_decode_128(int Tq);
 //           D = 64, 24 x 3600 (89 | 76 | 69).
 //   mid     D = 128 up to three rounds of 128-row workgroups: 16 x 4800
 //           (131 | 118 | 130), 12 x 7200 (198 | 179 | 208), 12 x 9600 (300 | 314 | -).
-enum class GridFill { sparse, small, mid, full };
+//   large   D = 64 from about two rounds of 256-row workgroups on, whose two row
+//           blocks per wave halve the LDS reads of K and V: 16 x 42240 (3765 | 4025),
+//           16 x 19200 (831 | 873), 7 x 42240 (1765 | 1837), 96 x 4800 (381 | 393);
+//           below, their last round costs more: 24 x 10560 (468 | 464), 16 x 14400
+//           (520 | 511), 4 x 42240 (1105 | 1090), 8 x 19200 (497 | 476).
+enum class GridFill { sparse, small, mid, full, large };
 inline GridFill grid_fill(int D, int BH, int Tk) {
   const long long tiles = (long long)BH * ((Tk + 63) / 64);
   if (tiles <= 256 && Tk >= (D == 128 ? 1536 : 512)) return GridFill::sparse;
   if (tiles <= (D == 64 ? 512 : 384) && Tk >= 2048) return GridFill::sparse;
   if (tiles <= (D == 128 ? 768 : (D == 72 ? 1152 : 1536))) return GridFill::small;
   if (D == 128 && tiles <= 1536) return GridFill::mid;
-  return GridFill::full;
+  return D == 64 && tiles > 4300 ? GridFill::large : GridFill::full;
 }
 // A cached call without a key-range split takes the training forward's 64-row
 // tiles up to 512 of them (two a CU); from there on it keeps the tiles of the
@@ -231,6 +236,7 @@ inline BwdGrid bwd_grid(int D, int BH, int T) {
 }
 // The training grids' configuration and work order (tile_item of mw_device.h), for
 // the host tests.
+int training_fwd_fill(int D, int BH, int T);
 int training_bwd_grid(int D, int BH, int T);
 void training_work_item(int bid, int BH, int& bh, int& rank);
 hipError_t launch_bwd_64(const BwdParams& p, hipStream_t stream);

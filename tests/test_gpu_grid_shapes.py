@@ -39,7 +39,8 @@ def test_work_order(mw, B, H, T, D, L):
 @pytest.mark.parametrize("B,H,T,D,L", [(1, 1, 5, 128, 3), (1, 2, 511, 64, 90), (1, 2, 513, 64, 90), (1, 1, 577, 72, 577),
                                        (1, 3, 1537, 128, 257), (1, 2, 2049, 72, 300), (2, 1, 2113, 64, 1),
                                        (6, 16, 513, 128, 130), (13, 16, 330, 64, 65), (12, 16, 400, 72, 100),
-                                       (11, 16, 300, 64, 70)])
+                                       (11, 16, 300, 64, 70), (30, 16, 213, 64, 40), (54, 16, 290, 64, 70),
+                                       (20, 16, 257, 72, 100)])
 def test_forward_tiles(mw, B, H, T, D, L):
     check(mw, B, H, T, D, L)
 

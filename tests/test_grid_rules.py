@@ -7,13 +7,26 @@ import pytest
 import paper_2608_01127_amd as mw
 import test_gpu_grid_shapes as shapes
 
+SPARSE, SMALL, MID, FULL, LARGE = range(5)
 WIDE, PAIRS, WIDE3, QUADS = 0, 2, 3, 4
 
 
-def bwd_grid(D, BH, T):
-    fn = mw.load()["_ZN2mw17training_bwd_gridEiii"]  # mw::training_bwd_grid(int, int, int)
+def rule(symbol):
+    fn = mw.load()[symbol]
     fn.restype, fn.argtypes = ctypes.c_int, [ctypes.c_int] * 3
-    return fn(D, BH, T)
+    return fn
+
+
+fwd_fill = rule("_ZN2mw17training_fwd_fillEiii")  # mw::training_fwd_fill(int, int, int)
+bwd_grid = rule("_ZN2mw17training_bwd_gridEiii")  # mw::training_bwd_grid(int, int, int)
+
+
+@pytest.mark.parametrize("D,BH,T,fill", [
+    (64, 16, 42240, LARGE), (64, 16, 19200, LARGE), (64, 7, 42240, LARGE), (64, 96, 4800, LARGE),
+    (64, 24, 10560, FULL), (64, 8, 19200, FULL), (64, 4, 42240, FULL), (72, 16, 19200, FULL), (128, 16, 42240, FULL),
+    (128, 16, 4800, MID), (72, 16, 3000, SMALL), (64, 4, 4000, SPARSE)])
+def test_forward_lines(D, BH, T, fill):
+    assert fwd_fill(D, BH, T) == fill
 
 
 # (heads, tokens) where one configuration measured at least 4% ahead of the next
@@ -42,3 +55,7 @@ def gpu_shapes():
 def test_gpu_shapes_reach_every_configuration():
     reached = {(D, bwd_grid(D, BH, T)) for D, BH, T in gpu_shapes()}
     assert reached == {(D, g) for D in (64, 72, 128) for g in (WIDE, PAIRS, QUADS)} | {(64, WIDE3)}
+    reached = {(D, fwd_fill(D, BH, T)) for D, BH, T in gpu_shapes()}
+    # (FULL at D = 128: the training shapes of test_gpu_train)
+    assert reached == {(D, f) for D in (64, 72, 128) for f in (SPARSE, SMALL)} | {(64, FULL), (64, LARGE), (72, FULL),
+                                                                               (128, MID)}
