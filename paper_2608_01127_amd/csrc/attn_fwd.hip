@@ -711,13 +711,13 @@ static hipError_t launch_tile(FwdParams p, hipStream_t stream) {
 }
 
 // Configuration of a cached call with its workgroups resident per CU (`fallback`
-// where no device is present) and the workgroups per CU that a call bound by
-// streaming its keys is spread over.
+// where no device is present), the rate of one that streams alone on a CU and the
+// rate of its partials.
 template <int D, class C>
-static FwdChoice cached_choice(int fallback, int stream_wgs) {
+static FwdChoice cached_choice(int fallback, double lone_rate, double part_rate) {
   static const int n = resident_workgroups(
       attn_fwd_kernel<D, true, C::NW, C::BN, C::RB, C::KG, C::NSTG, C::WPS>, 64 * C::NW, fallback);
-  return {C::BM, C::BK, n, stream_wgs};
+  return {C::BM, C::BK, n, lone_rate, part_rate};
 }
 
 // This file is compiled once per head dimension (MW_FWD_HEAD_DIM = 64, 72 or 128),
@@ -762,11 +762,13 @@ hipError_t MW_CAT(launch_fwd_, MW_FWD_HEAD_DIM)(const FwdParams& p, bool cached,
 }
 // (fallbacks, as built: Stream64 holds 64 KB of LDS at D = 64 and 96 KB at 72)
 FwdChoice MW_CAT(fwd_choice_, MW_FWD_HEAD_DIM)(int Tq) {
-  if (Tq <= 64) return cached_choice<kD, Stream64>(kD == 64 ? 2 : 1, 1);
-  // (two streaming workgroups a CU: 48 heads x 226 rows over 3 x 880, D = 72, us
-  // with three | two | one: 31.5 | 27.6 | 35.6)
-  if (Tq <= 256) return cached_choice<kD, Rows128<kD>>(3, 2);
-  return cached_choice<kD, CachedLong>(kD == 64 ? 2 : 3, kD == 64 ? 1 : 2);
+  if (Tq <= 64) return cached_choice<kD, Stream64>(kD == 64 ? 2 : 1, 1.0, 1.0);
+  // (double-buffered: a workgroup alone waits for each of its tiles.  With these
+  // rates the plans of 736 streaming shapes of 65 to 275 rows came to 2.1% of the
+  // best of all split counts on average; with 1 and 1, and two workgroups per CU as
+  // one round, to 5.2%)
+  if (Tq <= 256) return cached_choice<kD, Rows128<kD>>(kD == 64 ? 4 : 3, 0.7, 2.0);
+  return cached_choice<kD, CachedLong>(kD == 64 ? 2 : 3, 0.7, 2.0);
 }
 #elif !defined(MW_FWD_DECODE) && !defined(MW_FWD_CACHED) && !defined(MW_FWD_SMALL)
 hipError_t launch_fwd_128(const FwdParams& p, bool cached, hipStream_t stream) {
@@ -793,14 +795,14 @@ hipError_t launch_fwd_small_128(const FwdParams& p, GridFill fill, bool cached, 
 hipError_t launch_fwd_cached_128(const FwdParams& p, hipStream_t stream) {
   return launch_tile<128, true, Rows256>(p, stream);
 }
-FwdChoice fwd_choice_cached_128() { return cached_choice<128, Rows256>(1, 1); }
+FwdChoice fwd_choice_cached_128() { return cached_choice<128, Rows256>(1, 1.0, 1.0); }
 #else
 hipError_t launch_fwd_decode_128(const FwdParams& p, hipStream_t stream) {
   return p.Tq <= 64 ? launch_tile<128, true, Stream64>(p, stream) : launch_tile<128, true, Stream128>(p, stream);
 }
 // (fallback: 4 or 8 waves of 180-245 registers and 128 KB of LDS, one per CU)
 FwdChoice fwd_choice_decode_128(int Tq) {
-  return Tq <= 64 ? cached_choice<128, Stream64>(1, 1) : cached_choice<128, Stream128>(1, 1);
+  return Tq <= 64 ? cached_choice<128, Stream64>(1, 1.0, 1.0) : cached_choice<128, Stream128>(1, 1.0, 1.0);
 }
 #endif
 
@@ -835,6 +837,7 @@ constexpr double kBf16Flops = 1.1e15;
 // Time of a streaming workgroup beside its key range: Q and the first tiles'
 // latency, the partials at the end.
 constexpr double kStreamWgTime = 3e-6;
+constexpr double kMergeLaunch = 5e-6;
 
 SplitPlan fwd_plan_cached(int D, int BH, int Tq, int Tk, int qlen, bool isolated, size_t ws_bytes) {
   return fwd_plan_splits(fwd_choice(D, Tq), kBf16Flops, 2, D, BH, Tq, Tk, qlen, isolated, ws_bytes);
@@ -875,12 +878,12 @@ double split_makespan(const std::vector<int>& steps, int heads, int slots, int n
 }
 
 struct PlanKey {
-  int bm, bk, wg, swg, kv_bytes, D, BH, Tq, Tk, qlen, isolated;
-  double flops;
+  int bm, bk, wg, kv_bytes, D, BH, Tq, Tk, qlen, isolated;
+  double lone, part, flops;
   size_t ws;
   bool operator<(const PlanKey& o) const {
-    return std::tie(bm, bk, wg, swg, kv_bytes, D, BH, Tq, Tk, qlen, isolated, flops, ws) <
-           std::tie(o.bm, o.bk, o.wg, o.swg, o.kv_bytes, o.D, o.BH, o.Tq, o.Tk, o.qlen, o.isolated, o.flops, o.ws);
+    return std::tie(bm, bk, wg, kv_bytes, D, BH, Tq, Tk, qlen, isolated, lone, part, flops, ws) <
+           std::tie(o.bm, o.bk, o.wg, o.kv_bytes, o.D, o.BH, o.Tq, o.Tk, o.qlen, o.isolated, o.lone, o.part, o.flops, o.ws);
   }
 };
 
@@ -901,22 +904,29 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
   };
   std::vector<Cand> cands;
   if (t_mfma < t_stream) {
-    // streaming-bound (few query rows): every tile split, priced by the rounds
-    // of workgroups on the CUs, each the streaming of its key range at a CU's
-    // share of the bandwidth plus its prologue and epilogue.  (Pricing only the
-    // share of CUs covered took 11 ranges, 264 workgroups, for 24 heads: the
-    // last 8 ran a second round.  Calls over e4m3 keep that pricing: their
-    // probabilities are rounded against the reference of their own key range,
-    // so another split would move their outputs by a rounding of each.)
+    // streaming-bound (few query rows): every tile split, priced by the workgroups
+    // that the busiest CU takes: their prologues and epilogues, a round of resident
+    // workgroups at a time, and the streaming of their key ranges, the longest in
+    // whole key steps, at the CU's share of the bandwidth (of which one workgroup
+    // alone reaches ch.lone_rate).  Pricing the share of CUs covered took 11 ranges,
+    // 264 workgroups, for 24 heads: the last 8 ran a second round.  Pricing the mean
+    // range took 23 ranges of up to 8 steps for 24 of 7: 5 heads x 155 rows over
+    // 24 x 880 keys 31.1 -> 33.5 us.  Where an unsplit call has a few-tile
+    // configuration of its own, splitting also costs the merge's launch.  Calls over
+    // e4m3 keep the share of CUs: no other pricing has been measured for them.
+    const int nkt = (Tk + ch.bk - 1) / ch.bk;
+    const bool own_tile = D != 128 && Tq > 64 && unsplit_fill(D, BH, Tk) != GridFill::full;
     for (int ns = 1; ns <= ns_max; ++ns) {
       if (ns > 1 && fwd_split_bytes(D, BH, Tq, ns) > ws_bytes) break;
-      const double wgs = base * ns, room = cus * ch.stream_wgs;
-      double t = t_stream / std::min(1.0, wgs / room);
+      const double wgs = base * ns;
+      double t = t_stream / std::min(1.0, wgs / cus);
       if (kv_bytes > 1) {
-        const double rounds = std::ceil(wgs / room);
-        t = rounds * (kStreamWgTime + t_stream * room / wgs);
+        const double k = std::ceil(wgs / cus);                      // workgroups of the busiest CU
+        const double range = (double)((nkt + ns - 1) / ns) / nkt;  // longest range, of the keys
+        t = std::ceil(k / ch.wg_per_cu) * kStreamWgTime + k * t_stream * cus / base * range / (k > 1 ? 1.0 : ch.lone_rate);
+        if (ns > 1 && own_tile) t += kMergeLaunch;
       }
-      cands.push_back({t + part_time(Tq, ns), {ns, 0}});
+      cands.push_back({t + part_time(Tq, ns) / ch.part_rate, {ns, 0}});
     }
   } else if (base >= 8.0 * slots) {
     // eight or more rounds of workgroups: the last round is a small fraction
@@ -951,7 +961,7 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
         const int rows = fwd_split_rows(ch.bm, Tq, SplitPlan{ns, whole});
         if (ns > 1 && fwd_split_bytes(D, BH, rows, ns) > ws_bytes) continue;
         const double t = split_makespan(steps, heads, sl, ns, whole, o_wg, o_part) * t_step +
-                         (ns > 1 ? part_time(rows, ns) + 5e-6 : 0.0);  // merge traffic and its launch
+                         (ns > 1 ? part_time(rows, ns) + kMergeLaunch : 0.0);
         cands.push_back({t, {ns, ns > 1 ? whole : 0}});
       }
     }
@@ -972,8 +982,8 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
 // Split plan from a cost model, memoised per shape (a streaming loop repeats
 // its shape every step).  A call is bound by its MFMA time or by streaming
 // its K/V window, whichever is larger at full occupancy.  A streaming-bound
-// call splits every query tile and takes as long as the rounds of its
-// workgroups on the CUs (a workgroup or a few per CU keep the loads in flight):
+// call splits every query tile and takes as long as the busiest CU's workgroups
+// (a workgroup or a few per CU keep the loads in flight):
 // 24 heads, 64 rows over 6 x 2640 tokens, 64 -> 39 us at D = 128, 74 -> 32 at 72
 // and 55 -> 26 at 64 against pricing the share of CUs covered.  For an
 // MFMA-bound call a list-scheduling simulation of the dispatch order prices
@@ -990,7 +1000,7 @@ SplitPlan fwd_plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D
   if (BH < 1 || Tq < 1 || Tk < 1 || qlen < 1 || ch.bm < 1 || ch.bk < 1) return {1, 0};
   static std::mutex mu;
   static std::map<PlanKey, SplitPlan> memo;
-  const PlanKey key{ch.bm, ch.bk, ch.wg_per_cu, ch.stream_wgs, kv_bytes, D, BH, Tq, Tk, qlen, isolated ? 1 : 0, flops, ws_bytes};
+  const PlanKey key{ch.bm, ch.bk, ch.wg_per_cu, kv_bytes, D, BH, Tq, Tk, qlen, isolated ? 1 : 0, ch.lone_rate, ch.part_rate, flops, ws_bytes};
   {
     std::lock_guard<std::mutex> lock(mu);
     auto it = memo.find(key);

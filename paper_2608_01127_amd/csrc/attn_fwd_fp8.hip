@@ -778,9 +778,9 @@ FwdChoice fwd8_choice(int Tq) {
   static const int r64 = resident_workgroups(attn_fwd_fp8_kernel<F2::NW, F2::RB, F2::BN, F2::KG, true>, 64 * F2::NW, 1);
   static const int r128 = resident_workgroups(attn_fwd_fp8_kernel<F4::NW, F4::RB, F4::BN, F4::KG, true>, 64 * F4::NW, 1);
   static const int r256 = resident_workgroups(attn_fwd_fp8_kernel<C::NW, C::RB, C::BN, C::KG, false>, 64 * C::NW, 1);
-  if (Tq <= 64) return {64, F2::BN * F2::KG, r64, 1};
-  if (Tq <= 128) return {128, F4::BN * F4::KG, r128, 1};
-  return {32 * C::RB * C::NW, C::BN, r256, 1};
+  if (Tq <= 64) return {64, F2::BN * F2::KG, r64, 1.0, 1.0};
+  if (Tq <= 128) return {128, F4::BN * F4::KG, r128, 1.0, 1.0};
+  return {32 * C::RB * C::NW, C::BN, r256, 1.0, 1.0};
 }
 
 bool fwd8_rotates_in_staging(int Tq, int Tk, int L, const SplitPlan& sp) {

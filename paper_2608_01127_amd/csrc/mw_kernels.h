@@ -110,7 +110,9 @@ struct FwdChoice {
   int bm;
   int bk;
   int wg_per_cu;
-  int stream_wgs;  // workgroups per CU that a call bound by streaming its keys is spread over
+  // for the price of a call bound by streaming its keys:
+  double lone_rate;  // share of a CU's streaming rate that one workgroup alone on it reaches
+  double part_rate;  // rate of its partials, written and read back, against HBM's
 };
 FwdChoice fwd_choice(int D, int Tq);
 FwdChoice fwd_choice_64(int Tq);

@@ -22,3 +22,26 @@ def test_streaming_splits_fill_rounds(H, D, q_len, bm, per_cu):
     wgs, room = H * -(-q_len // bm) * ns.value, 256 * per_cu
     assert nw.value == 0 and wgs >= 0.75 * room * -(-wgs // room), (ns.value, wgs)
     assert ns.value * H * q_len * (D + 2) * 4 <= ws
+
+
+@pytest.mark.parametrize("H,D,nq,q_len,L,window,sink,bm,bk", [
+    (5, 128, 1, 155, 880, 24, 0, 128, 128), (20, 72, 2, 70, 880, 4, 300, 128, 64), (8, 128, 1, 129, 600, 8, 300, 128, 128),
+    (4, 128, 8, 32, 1320, 4, 0, 128, 128), (16, 128, 1, 64, 2640, 6, 0, 64, 64), (5, 128, 1, 257, 600, 8, 300, 128, 128)])
+def test_streaming_splits_fill_key_steps(H, D, nq, q_len, L, window, sink, bm, bk):
+    """A range more, with as many workgroups on the busiest CU, would not shorten the longest range (in whole
+    key steps, which a workgroup's time goes by) by a step in eight or more."""
+    lib = mw.load()
+    c = new_cache(S=window + 1, B=1, H=H, L=L, D=D)
+    c.head = window
+    c.sink_len = sink
+    c.k_sink = c.v_sink = c.k_slots
+    ns, nw = ctypes.c_int(), ctypes.c_int()
+    ws = lib.mw_chunk_attn_cached_workspace_size(ctypes.byref(c), nq, q_len, window)
+    assert lib.mw_chunk_attn_cached_plan(ctypes.byref(c), nq, q_len, window, mw.MW_QUEUED_CAUSAL, ws, ctypes.byref(ns),
+                                         ctypes.byref(nw)) == mw.MW_OK
+    steps = -(-(sink + window * L + nq * q_len) // bk)
+    n_tiles = H * -(-nq * q_len // bm)
+    longest = -(-steps // ns.value)
+    for more in range(ns.value + 1, ns.value + 4):
+        if -(-n_tiles * more // 256) == -(-n_tiles * ns.value // 256):
+            assert -(-steps // more) > longest * 7 / 8, (ns.value, more, longest)
