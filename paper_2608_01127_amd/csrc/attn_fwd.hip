@@ -732,10 +732,13 @@ static FwdChoice cached_choice(int fallback, double lone_rate, double part_rate)
 // sharing one with the 256-row training kernel moves its loop relative to the
 // instruction-cache lines, which cost it 1.7%.
 //
-// Training calls pick their tile by grid_fill; so do cached calls without a
-// key-range split up to 512 tiles (unsplit_fill), on heads and keys only: over
-// a whole history they visit the keys in the training call's order and give
-// its rows bit for bit.
+// Training calls pick their tile by grid_fill, cached calls without a key-range
+// split by unsplit_tile, and split ones by their rows (fwd_choice).
+static UnsplitTile call_tile(int D, const FwdParams& p) {
+  if (p.n_splits > 1) return UnsplitTile::plan;
+  return unsplit_tile(D, p.BH, p.Tq, p.Tk, p.vis_mode != VIS_QUEUED_ISOLATED || p.Tq <= p.qlen);
+}
+
 #if MW_FWD_HEAD_DIM != 128
 #define MW_CAT_(a, b) a##b
 #define MW_CAT(a, b) MW_CAT_(a, b)
@@ -745,8 +748,8 @@ constexpr int kD = MW_FWD_HEAD_DIM;
 // 128-row ones; 48 x 226 over 3 x 880: 28.6 | 25.9)
 using CachedLong = std::conditional_t<kD == 64, Rows256x2, Rows128<kD>>;
 hipError_t MW_CAT(launch_fwd_, MW_FWD_HEAD_DIM)(const FwdParams& p, bool cached, hipStream_t stream) {
-  const GridFill fill = cached ? unsplit_fill(kD, p.BH, p.Tk) : grid_fill(kD, p.BH, p.Tk);
   if (!cached) {
+    const GridFill fill = grid_fill(kD, p.BH, p.Tk);
     if (fill == GridFill::sparse) return launch_tile<kD, false, Rows64x8>(p, stream);
     if (fill == GridFill::small) return launch_tile<kD, false, Rows64<kD>>(p, stream);
     if constexpr (kD == 64) {
@@ -754,9 +757,10 @@ hipError_t MW_CAT(launch_fwd_, MW_FWD_HEAD_DIM)(const FwdParams& p, bool cached,
     }
     return launch_tile<kD, false, Rows128<kD>>(p, stream);
   }
-  if (p.Tq <= 64) return launch_tile<kD, true, Stream64>(p, stream);
-  if (p.n_splits <= 1 && fill == GridFill::sparse) return launch_tile<kD, true, Rows64x8>(p, stream);
-  if (p.n_splits <= 1 && fill == GridFill::small) return launch_tile<kD, true, Rows64<kD>>(p, stream);
+  const UnsplitTile tile = call_tile(kD, p);
+  if (tile == UnsplitTile::groups4) return launch_tile<kD, true, Rows64x8>(p, stream);
+  if (tile == UnsplitTile::groups2) return launch_tile<kD, true, Rows64<kD>>(p, stream);
+  if (p.Tq <= 64 && tile != UnsplitTile::rows128) return launch_tile<kD, true, Stream64>(p, stream);
   if (p.Tq <= 256) return launch_tile<kD, true, Rows128<kD>>(p, stream);
   return launch_tile<kD, true, CachedLong>(p, stream);
 }
@@ -772,24 +776,25 @@ FwdChoice MW_CAT(fwd_choice_, MW_FWD_HEAD_DIM)(int Tq) {
 }
 #elif !defined(MW_FWD_DECODE) && !defined(MW_FWD_CACHED) && !defined(MW_FWD_SMALL)
 hipError_t launch_fwd_128(const FwdParams& p, bool cached, hipStream_t stream) {
-  const GridFill fill = cached ? unsplit_fill(128, p.BH, p.Tk) : grid_fill(128, p.BH, p.Tk);
   if (!cached) {
-    if (fill != GridFill::full) return launch_fwd_small_128(p, fill, false, stream);
+    const GridFill fill = grid_fill(128, p.BH, p.Tk);
+    if (fill != GridFill::full) return launch_fwd_small_128(p, fill, stream);
     return launch_tile<128, false, Rows256>(p, stream);
   }
   if (p.Tq <= 512) return launch_fwd_decode_128(p, stream);
-  if (p.n_splits <= 1 && fill != GridFill::full) return launch_fwd_small_128(p, fill, true, stream);
+  const UnsplitTile tile = call_tile(128, p);
+  if (tile != UnsplitTile::plan) return launch_fwd_unsplit_128(p, tile, stream);
   return launch_fwd_cached_128(p, stream);
 }
 #elif defined(MW_FWD_SMALL)
-hipError_t launch_fwd_small_128(const FwdParams& p, GridFill fill, bool cached, hipStream_t stream) {
-  if (cached) {
-    if (fill == GridFill::sparse) return launch_tile<128, true, Rows64x8>(p, stream);
-    return launch_tile<128, true, Rows64<128>>(p, stream);
-  }
+hipError_t launch_fwd_small_128(const FwdParams& p, GridFill fill, hipStream_t stream) {
   if (fill == GridFill::sparse) return launch_tile<128, false, Rows64x8>(p, stream);
   if (fill == GridFill::small) return launch_tile<128, false, Rows64<128>>(p, stream);
   return launch_tile<128, false, Rows128<128>>(p, stream);
+}
+hipError_t launch_fwd_unsplit_128(const FwdParams& p, UnsplitTile tile, hipStream_t stream) {
+  if (tile == UnsplitTile::groups4) return launch_tile<128, true, Rows64x8>(p, stream);
+  return launch_tile<128, true, Rows64<128>>(p, stream);
 }
 #elif defined(MW_FWD_CACHED)
 hipError_t launch_fwd_cached_128(const FwdParams& p, hipStream_t stream) {
@@ -814,6 +819,9 @@ FwdChoice fwd_choice(int D, int Tq) {
 }
 
 int training_fwd_fill(int D, int BH, int T) { return (int)grid_fill(D, BH, T); }
+int cached_unsplit_tile(int D, int BH, int Tq, int Tk, int training_rows) {
+  return (int)unsplit_tile(D, BH, Tq, Tk, training_rows != 0);
+}
 void training_work_item(int bid, int BH, int& bh, int& rank) { tile_item(bid, BH, bh, rank); }
 
 hipError_t launch_combine(const FwdParams& p, int D, hipStream_t stream) {
@@ -903,6 +911,9 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
     SplitPlan sp;
   };
   std::vector<Cand> cands;
+  const UnsplitTile unsplit =
+      kv_bytes > 1 ? unsplit_tile(D, BH, Tq, Tk, !isolated || Tq <= qlen) : UnsplitTile::plan;
+  const bool own_groups = unsplit == UnsplitTile::groups4 || unsplit == UnsplitTile::groups2;
   if (t_mfma < t_stream) {
     // streaming-bound (few query rows): every tile split, priced by the workgroups
     // that the busiest CU takes: their prologues and epilogues, a round of resident
@@ -915,7 +926,6 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
     // configuration of its own, splitting also costs the merge's launch.  Calls over
     // e4m3 keep the share of CUs: no other pricing has been measured for them.
     const int nkt = (Tk + ch.bk - 1) / ch.bk;
-    const bool own_tile = D != 128 && Tq > 64 && unsplit_fill(D, BH, Tk) != GridFill::full;
     for (int ns = 1; ns <= ns_max; ++ns) {
       if (ns > 1 && fwd_split_bytes(D, BH, Tq, ns) > ws_bytes) break;
       const double wgs = base * ns;
@@ -924,7 +934,8 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
         const double k = std::ceil(wgs / cus);                      // workgroups of the busiest CU
         const double range = (double)((nkt + ns - 1) / ns) / nkt;  // longest range, of the keys
         t = std::ceil(k / ch.wg_per_cu) * kStreamWgTime + k * t_stream * cus / base * range / (k > 1 ? 1.0 : ch.lone_rate);
-        if (ns > 1 && own_tile) t += kMergeLaunch;
+        if (ns > 1 && own_groups && Tq > 64) t += kMergeLaunch;
+        if (ns == 1 && unsplit == UnsplitTile::rows128) t *= 1.35;  // against a split plan's 64-row tiles
       }
       cands.push_back({t + part_time(Tq, ns) / ch.part_rate, {ns, 0}});
     }
@@ -953,11 +964,13 @@ SplitPlan plan_splits(const FwdChoice& ch, double flops, int kv_bytes, int D, in
     const int heads = per_xcd ? BH / 8 : BH;
     const int sl = (int)slots / (per_xcd ? 8 : 1);
     // more than four rounds of workgroups gain nothing; at most 48 whole-tile
-    // counts per split count are priced (every one up to 48 query tiles)
+    // counts per split count are priced (every one up to 48 query tiles), and none
+    // but 0 where an unsplit call splits its keys among wave groups, which whole
+    // tiles do not: a row's bits then depend only on whether it was split
     const int ns_cap = std::min(ns_max, std::max(8, (int)std::ceil(4.0 * slots / base)));
     const int stride = (nqt + 47) / 48;
     for (int ns = 1; ns <= ns_cap; ++ns) {
-      for (int whole = ns == 1 ? nqt : 0; whole <= (ns == 1 ? nqt : nqt - 1); whole += (ns == 1 ? 1 : stride)) {
+      for (int whole = ns == 1 ? nqt : 0; whole <= (ns == 1 ? nqt : own_groups ? 0 : nqt - 1); whole += (ns == 1 ? 1 : stride)) {
         const int rows = fwd_split_rows(ch.bm, Tq, SplitPlan{ns, whole});
         if (ns > 1 && fwd_split_bytes(D, BH, rows, ns) > ws_bytes) continue;
         const double t = split_makespan(steps, heads, sl, ns, whole, o_wg, o_part) * t_step +

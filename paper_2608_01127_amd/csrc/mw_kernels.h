@@ -97,7 +97,9 @@ hipError_t launch_fwd_cached_128(const FwdParams& p, hipStream_t stream);
 hipError_t launch_fwd_decode_128(const FwdParams& p, hipStream_t stream);
 // the D = 128 tiles for grids that do not fill the card
 enum class GridFill;
-hipError_t launch_fwd_small_128(const FwdParams& p, GridFill fill, bool cached, hipStream_t stream);
+hipError_t launch_fwd_small_128(const FwdParams& p, GridFill fill, hipStream_t stream);
+enum class UnsplitTile;
+hipError_t launch_fwd_unsplit_128(const FwdParams& p, UnsplitTile tile, hipStream_t stream);
 inline hipError_t launch_fwd(const FwdParams& p, int D, bool cached, hipStream_t stream) {
   return D == 64 ? launch_fwd_64(p, cached, stream)
                  : (D == 72 ? launch_fwd_72(p, cached, stream) : launch_fwd_128(p, cached, stream));
@@ -149,11 +151,26 @@ inline GridFill grid_fill(int D, int BH, int Tk) {
   if (D == 128 && tiles <= 1536) return GridFill::mid;
   return D == 64 && tiles > 4300 ? GridFill::large : GridFill::full;
 }
-// A cached call without a key-range split takes the training forward's 64-row
-// tiles up to 512 of them (two a CU); from there on it keeps the tiles of the
-// split plans, whose whole tiles an unsplit call then gives bit for bit.
-inline GridFill unsplit_fill(int D, int BH, int Tk) {
-  return (long long)BH * ((Tk + 63) / 64) <= 512 ? grid_fill(D, BH, Tk) : GridFill::full;
+// Tile of a cached call without a key-range split: that of the split plans
+// (fwd_choice), whose whole tiles the call then gives bit for bit, or one of its
+// own, as the training forward has for the same heads and keys.  `training_rows`:
+// the call's rows see their keys as training rows do (queued-causal, or one queued
+// chunk).  At D = 64 and 72, and at D = 128 for more than 512 rows, such a call then
+// splits each key step among as many wave groups as the training forward, and over
+// a whole history gives its rows bit for bit.  us against the split plans' tiles, D =
+// 64 | 72: 24 heads x 600 rows over 1800 keys 24 for 44 | 27 for 37, 40 x 256 over
+// 1456 21 for 29 | 24 for 32, 8 x 64 over 3664 31 for 45 | 36 for 57; for the rows'
+// sake 64 x 64 over 3664 62 for 45 | 70 for 59.  Other calls of more than 64 rows have
+// the groups up to 512 64-row tiles (two a CU).
+enum class UnsplitTile { plan = 0, groups4, groups2, rows128 };
+inline UnsplitTile unsplit_tile(int D, int BH, int Tq, int Tk, bool training_rows) {
+  if (D == 128 && Tq <= 512) return UnsplitTile::plan;
+  if (!training_rows && (Tq <= 64 || (long long)BH * ((Tk + 63) / 64) > 512)) return UnsplitTile::plan;
+  const GridFill fill = grid_fill(D, BH, Tk);
+  if (fill == GridFill::sparse) return UnsplitTile::groups4;
+  // (64 rows of a split plan have the two groups too)
+  if (fill == GridFill::small) return Tq <= 64 ? UnsplitTile::plan : UnsplitTile::groups2;
+  return D != 128 && Tq <= 64 ? UnsplitTile::rows128 : UnsplitTile::plan;
 }
 // fp8 (e4m3) cached attention at D = 128: its tile configuration and launcher
 // (FwdParams as described above), and the merge of split partials (D = 128).
@@ -236,9 +253,10 @@ inline BwdGrid bwd_grid(int D, int BH, int T) {
   if (D == 64 && (tiles > 1130 || (tiles > 900 && T <= 3200))) return BwdGrid::wide3;
   return BwdGrid::wide;
 }
-// The training grids' configuration and work order (tile_item of mw_device.h), for
+// The rules above and the training grids' work order (tile_item of mw_device.h), for
 // the host tests.
 int training_fwd_fill(int D, int BH, int T);
+int cached_unsplit_tile(int D, int BH, int Tq, int Tk, int training_rows);
 int training_bwd_grid(int D, int BH, int T);
 void training_work_item(int bid, int BH, int& bh, int& rank);
 hipError_t launch_bwd_64(const BwdParams& p, hipStream_t stream);

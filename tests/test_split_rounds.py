@@ -45,3 +45,26 @@ def test_streaming_splits_fill_key_steps(H, D, nq, q_len, L, window, sink, bm, b
     for more in range(ns.value + 1, ns.value + 4):
         if -(-n_tiles * more // 256) == -(-n_tiles * ns.value // 256):
             assert -(-steps // more) > longest * 7 / 8, (ns.value, more, longest)
+
+
+@pytest.mark.parametrize("mode", [mw.MW_QUEUED_CAUSAL, mw.MW_QUEUED_ISOLATED])
+@pytest.mark.parametrize("D", [64, 72, 128])
+def test_whole_tiles_only_where_an_unsplit_call_has_them(D, mode):
+    """A whole tile of a split plan is what the unsplit call computes for its rows, bit for bit:
+    no plan keeps one where the unsplit call splits its keys among wave groups."""
+    unsplit_tile = mw.load()["_ZN2mw19cached_unsplit_tileEiiiii"]
+    unsplit_tile.restype, unsplit_tile.argtypes = ctypes.c_int, [ctypes.c_int] * 5
+    lib, seen = mw.load(), set()
+    for H in (1, 3, 6, 8, 12, 16, 24):
+        for window in (1, 2, 3):
+            for nq, q_len in ((1, 900), (2, 700), (3, 500), (3, 1500), (5, 600), (8, 300)):
+                c = new_cache(S=4, B=1, H=H, L=q_len, D=D)
+                c.head = window
+                ns, nw = ctypes.c_int(), ctypes.c_int()
+                ws = lib.mw_chunk_attn_cached_workspace_size(ctypes.byref(c), nq, q_len, window)
+                assert lib.mw_chunk_attn_cached_plan(ctypes.byref(c), nq, q_len, window, mode, ws, ctypes.byref(ns),
+                                                     ctypes.byref(nw)) == mw.MW_OK
+                own = unsplit_tile(D, H, nq * q_len, (window + nq) * q_len, int(mode == mw.MW_QUEUED_CAUSAL or nq == 1))
+                seen.add((own, nw.value > 0))
+                assert own == 0 or nw.value == 0, (H, window, nq, q_len, ns.value, nw.value)
+    assert (1, False) in seen and (2, False) in seen
