@@ -193,13 +193,17 @@ def _strides(*ts):
     return _strides_array(*[t.stride() for t in ts])
 
 
-def _plain_views(ts, shape, index) -> bool:
-    """Whether every tensor is a bf16 [B,H,T,D] view of `shape` on GPU `index` with a contiguous
+def _plain_views(ts, shape, ref) -> bool:
+    """Whether every tensor is a bf16 [B,H,T,D] view of `shape` on the GPU of `ref` with a contiguous
     last dimension: what the checks below find one by one, in a sixth of their time.  A call
     whose tensors are not goes through them, for their errors."""
-    if index < 0 or len(shape) != 4:
+    torch = _torch()
+    if not isinstance(ref, torch.Tensor) or len(shape) != 4:
         return False
-    bf16 = _torch().bfloat16
+    index = ref.get_device()
+    if index < 0:
+        return False
+    bf16 = torch.bfloat16
     for t in ts:
         if t.dtype is not bf16 or t.shape != shape or t.get_device() != index or t.stride()[-1] != 1:
             return False
@@ -230,7 +234,7 @@ def mw_block_causal_attn_fwd(q, k, v, chunk_len: int, scale=None, out=None, lse=
     """Block-causal attention forward.  q, k, v: bf16 [B,H,T,D] (views with a
     contiguous head dimension are read in place).  Returns (o, lse)."""
     torch = _torch()
-    plain = _plain_views((q, k, v) if out is None else (q, k, v, out), q.shape, q.get_device())
+    plain = _plain_views((q, k, v) if out is None else (q, k, v, out), q.shape, q)
     if not plain:
         for n, t in (("q", q), ("k", k), ("v", v)):
             _bf16_4d(n, t, view=True)
@@ -263,7 +267,7 @@ def mw_block_causal_attn_bwd(q, k, v, o, d_o, lse, chunk_len: int, scale=None, w
     """Backward of mw_block_causal_attn_fwd.  Returns (dq, dk, dv), bf16 [B,H,T,D]
     (views with a contiguous head dimension are accepted for every tensor)."""
     torch = _torch()
-    plain = _plain_views([t for t in (q, k, v, o, d_o, dq, dk, dv) if t is not None], q.shape, q.get_device())
+    plain = _plain_views([t for t in (q, k, v, o, d_o, dq, dk, dv) if t is not None], q.shape, q)
     if not plain:
         for n, t in (("q", q), ("k", k), ("v", v), ("o", o), ("d_o", d_o)):
             _bf16_4d(n, t, view=True)
@@ -389,7 +393,7 @@ def mw_kvcache_append(cache: KVCache, k_chunk, v_chunk) -> int:
     """Commit one chunk (bf16 [B,H,L,D], or a view of one with a contiguous head
     dimension); returns the slot it was written to."""
     d = cache.desc
-    if not _plain_views((k_chunk, v_chunk), (d.B, d.H, d.L, d.D), cache.k_slots.get_device()):
+    if not _plain_views((k_chunk, v_chunk), (d.B, d.H, d.L, d.D), cache.k_slots):
         for n, t in (("k_chunk", k_chunk), ("v_chunk", v_chunk)):
             _bf16_4d(n, t, view=True)
             if tuple(t.shape) != (d.B, d.H, d.L, d.D):
@@ -450,7 +454,7 @@ def mw_chunk_attn_cached(q, k_new, v_new, n_queued: int, q_len: int, cache: KVCa
     torch = _torch()
     d = cache.desc
     plain = _plain_views((q, k_new, v_new) if out is None else (q, k_new, v_new, out),
-                         (d.B, d.H, n_queued * q_len, d.D), cache.k_slots.get_device())
+                         (d.B, d.H, n_queued * q_len, d.D), cache.k_slots)
     if not plain:
         for n, t in (("q", q), ("k_new", k_new), ("v_new", v_new)):
             _bf16_4d(n, t, view=True)

@@ -479,3 +479,18 @@ def test_lse_output_checks():
             _lib._check_lse(t, shape, dev)
     with pytest.raises(ValueError):
         _lib._check_lse(torch.empty(shape, dtype=torch.float32), shape, torch.device("meta"))
+
+
+def test_arrays_are_refused_as_a_wrong_type():
+    """A numpy array in a tensor's place is refused with the type it has, as any other dtype is."""
+    import numpy as np
+    import torch
+    a = np.zeros((1, 1, 4, 64), np.uint16)
+    with pytest.raises(TypeError, match="q must be bfloat16"):
+        _lib.mw_block_causal_attn_fwd(a, a, a, 4)
+    lse = torch.empty((1, 1, 4), dtype=torch.float32)
+    with pytest.raises(TypeError, match="q must be bfloat16"):
+        _lib.mw_block_causal_attn_bwd(a, a, a, a, a, lse, 4)
+    t = torch.zeros((1, 1, 4, 64), dtype=torch.bfloat16)
+    with pytest.raises(ValueError, match="GPU"):  # a CPU tensor: by its device
+        _lib.mw_block_causal_attn_fwd(t, t, t, 4)
