@@ -598,11 +598,11 @@ struct FwdTile {
 // waves of two row blocks.
 using Rows256 = FwdTile<8, 64, 1, 1, 2, 1>;
 using Rows256x2 = FwdTile<4, 64, 2, 1, 2, 2>;
-// 128 rows, four waves.  D = 64 and 72 at three waves per SIMD (<= 168
-// registers): D = 72 training (16 heads x 19200) 1098 -> 1037 us against eight
-// waves of 256 rows, whose barriers hold two waves per SIMD in step; D = 64
-// (24 heads x 10560) 439 -> 433 against two row blocks per wave, (24 x 4000)
-// 95 -> 81.  D = 128 at two.
+// 128 rows, four waves.  D = 64 at four waves per SIMD (124 registers) and 72 at
+// three (160): D = 72 training (16 heads x 19200) 1098 -> 1037 us against eight waves
+// of 256 rows, whose barriers hold two waves per SIMD in step; D = 64 (24 heads x
+// 10560) 439 -> 433 against two row blocks per wave, (24 x 4000) 95 -> 81.  D = 128 at
+// two.
 template <int D>
 using Rows128 = FwdTile<4, 64, 1, 1, 2, D == 128 ? 2 : 3>;
 // 64 rows, four waves in two key groups, 64 keys per step: half the rows and

@@ -135,7 +135,7 @@ FwdChoice fwd_choice_decode_128(int Tq);
 //   small   up to 1.5 rounds of resident 64-row workgroups: D = 128, 24 x 2000
 //           (56 | 47 | 47); D = 72, 16 x 3000 (67 | 53 | 43), 24 x 3600 (94 | 90 | 90);
 //           D = 64, 24 x 3600 (89 | 76 | 69).
-//   mid     D = 128 up to three rounds of 128-row workgroups: 16 x 4800
+//   mid     D = 128 up to 1.5 rounds of resident 128-row workgroups: 16 x 4800
 //           (131 | 118 | 130), 12 x 7200 (198 | 179 | 208), 12 x 9600 (300 | 314 | -).
 //   large   D = 64 from about two rounds of 256-row workgroups on, whose two row
 //           blocks per wave halve the LDS reads of K and V: 16 x 42240 (3765 | 4025),

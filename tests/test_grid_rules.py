@@ -11,6 +11,36 @@ SPARSE, SMALL, MID, FULL, LARGE = range(5)
 WIDE, PAIRS, WIDE3, QUADS = 0, 2, 3, 4
 
 
+class Choice(ctypes.Structure):  # mw::FwdChoice
+    _fields_ = [("bm", ctypes.c_int), ("bk", ctypes.c_int), ("wg_per_cu", ctypes.c_int),
+                ("lone_rate", ctypes.c_double), ("part_rate", ctypes.c_double)]
+
+
+# (head width, queued rows): rows and keys of the cached tile, and workgroups resident per CU
+CHOICES = [(64, 64, 64, 64, 2), (64, 65, 128, 64, 4), (64, 257, 256, 64, 2), (72, 64, 64, 64, 1), (72, 65, 128, 64, 3),
+           (72, 257, 128, 64, 3), (128, 64, 64, 64, 1), (128, 65, 128, 128, 1), (128, 513, 256, 64, 1)]
+
+
+def check_choice(D, Tq, bm, bk, wgs):
+    fn = mw.load()["_ZN2mw10fwd_choiceEii"]  # mw::fwd_choice(int, int)
+    fn.restype, fn.argtypes = Choice, [ctypes.c_int] * 2
+    c = fn(D, Tq)
+    assert (c.bm, c.bk, c.wg_per_cu) == (bm, bk, wgs)
+
+
+@pytest.mark.parametrize("D,Tq,bm,bk,wgs", CHOICES)
+def test_residency_assumed_without_a_device(D, Tq, bm, bk, wgs):
+    check_choice(D, Tq, bm, bk, wgs)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,Tq,bm,bk,wgs", CHOICES)
+def test_residency_on_the_device(mw, D, Tq, bm, bk, wgs):
+    """The runtime's occupancy of the built kernels is what is assumed where no device is present, so
+    that plans and workspace sizes made there hold here."""
+    check_choice(D, Tq, bm, bk, wgs)
+
+
 def rule(symbol):
     fn = mw.load()[symbol]
     fn.restype, fn.argtypes = ctypes.c_int, [ctypes.c_int] * 3
