@@ -14,7 +14,7 @@
 //   row(t, s) = 16*t + 4*(s/8) + 8*((s%8)/4) + s%4,     s = 0..15,
 // which is exactly the set of rows held in registers 8t..8t+7 of each lane.
 // The matching A operand is read from a row-major LDS tile with two
-// transposing reads (lds_tr8 below).
+// transposing reads (FragOffsets::tr8 below).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -96,43 +96,12 @@ struct Tile {
   }
 };
 
-// 16-byte load of the A/B operand "row r, columns c..c+7" from an LDS tile.
-template <int D>
-__device__ __forceinline__ bf16x8 lds_row8(const bf16_t* tile, int r, int c) {
-  return *reinterpret_cast<const bf16x8*>(tile + Tile<D>::off(r, c));
-}
-
-// A operand [m = column of the tile][k = slot] for contraction step t, taken
-// from an LDS tile whose rows are the contraction index:
-//   lane l gets tile[row(t, 8*(l/32) + j)][c0 + l%32], j = 0..7,
-// with row() the slot binding described at the top of this file.  `rbase` is
-// the tile row of slot row 0 (a multiple of 32 plus 16*t is added inside).
-template <int D>
-__device__ __forceinline__ bf16x8 lds_tr8(const bf16_t* tile, int rbase, int t, int c0, int lane) {
-  const int rr = rbase + 16 * t + 4 * (lane >> 5) + ((lane & 15) >> 2);
-  const int cc = c0 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const bf16_t* p0 = tile + Tile<D>::off(rr, cc);
-  const bf16_t* p1 = tile + Tile<D>::off(rr + 8, cc);
-  i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MW_LDS i16x4*)(p0));
-  i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MW_LDS i16x4*)(p1));
-  bf16x8 r;
-  bf16x4 lo4 = __builtin_bit_cast(bf16x4, lo);
-  bf16x4 hi4 = __builtin_bit_cast(bf16x4, hi);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    r[j] = lo4[j];
-    r[4 + j] = hi4[j];
-  }
-  return r;
-}
-
-// Per-lane element offsets of a wave's fragment reads from an LDS tile, for
-// kernels that compute them once: the row read of lds_row8 (row l % 32,
-// columns 16 kk + 8 (l / 32)) per 16-column step kk, and the two transposing
-// reads of lds_tr8 (rows rr and rr + 8, column block db).  The slot swizzle
-// repeats every 16 rows, so a read of rows further down the tile (a later
-// 32-row block, the second 16-row contraction step) is the same register plus
-// a constant offset that the compiler folds into the instruction.
+// Per-lane element offsets of a wave's fragment reads from an LDS tile, computed
+// once: the row read (row l % 32, columns 16 kk + 8 (l / 32)) per 16-column step kk,
+// and the two transposing reads (rows rr and rr + 8) of column block db.  The slot
+// swizzle repeats every 16 rows, so a read of rows further down the tile (a later
+// 32-row block, the second 16-row contraction step) is the same register plus a
+// constant offset that the compiler folds into the instruction.
 template <int D>
 struct FragOffsets {
   static constexpr int KK = (D + 15) / 16, DB = D / 32;
@@ -148,16 +117,19 @@ struct FragOffsets {
       tr[db][1] = Tile<D>::off(rr + 8, cc) + extra;
     }
   }
-  // lds_row8(tile, rbase + l % 32, 16 kk + 8 (l / 32)), rbase a multiple of 16
+  // A/B operand: lane l gets row rbase + l % 32, columns 16 kk + 8 (l / 32) + 0..7, rbase
+  // a multiple of 16
   __device__ __forceinline__ bf16x8 row8(const bf16_t* tile, int rbase, int kk) const {
     return *reinterpret_cast<const bf16x8*>(tile + row[kk] + rbase * D);
   }
-  // lds_tr8(tile, rbase, t, 32 db, l), rbase a multiple of 16
+  // A operand [m = column][k = slot] of contraction step t, from a tile whose rows are
+  // the contraction index: lane l gets tile[rbase + row(t, 8 (l / 32) + j)][32 db + l % 32],
+  // j = 0..7, with row() the slot binding at the top of this file; rbase a multiple of 16
   __device__ __forceinline__ bf16x8 tr8(const bf16_t* tile, int rbase, int t, int db) const;
 };
 
-// The same A operand from the two addresses lds_tr8 computes (rows rr and
-// rr + 8 of the tile at column cc), for callers that precompute them.
+// The two transposing reads of an A operand (tr8): p0 and p1 address rows rr and rr + 8
+// of the tile at column cc.
 __device__ __forceinline__ bf16x8 lds_tr8_at(const bf16_t* p0, const bf16_t* p1) {
   i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MW_LDS i16x4*)(p0));
   i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MW_LDS i16x4*)(p1));
