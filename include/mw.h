@@ -27,6 +27,10 @@
  *     evict, set_sink, rope_shift) must run outside it, and a recorded
  *     attention call keeps the ring state (window, pending re-shifts) it was
  *     recorded with.
+ *   - Results are deterministic: a call repeated gives the same bits.  How the
+ *     work of an attention call is divided goes by its sizes (B, H, the rows
+ *     and the keys), so a row may differ, within its rounding, from the same
+ *     row in a call with other heads or of another length.
  *   - Arguments are validated before anything is enqueued; on error nothing
  *     is enqueued, no state changes, and a negative mw_status is returned.
  *     mw_last_error() then describes the problem (per-thread message).
@@ -293,8 +297,12 @@ int mw_kvcache_slot_of(const mw_kvcache* c, int64_t chunk);
  *                      tiles may run unsplit while the lighter ones, which run
  *                      last, are split (mw_chunk_attn_cached_plan).  NULL or a
  *                      smaller buffer: a plan that fits (possibly no split).
- *                      The result does not depend on the plan beyond fp32
- *                      rounding.
+ *                      The result does not depend on the plan beyond the
+ *                      rounding of fp32 sums and of the probabilities.
+ * Without a split, over a window that holds the whole history (no sink,
+ * q_len = L, MW_QUEUED_CAUSAL or one queued chunk) the result is that of
+ * mw_block_causal_attn_fwd's last rows on the same heads and keys, bit for bit,
+ * at D = 64 and 72, and at D = 128 for more than 512 queued rows.
  * Keys are visited in logical order whatever the ring offset, so the result
  * for a given window content does not depend on where the ring wrapped.
  * Errors: MW_EINVAL (null pointers, n_queued/q_len < 1, window > live,
@@ -317,7 +325,8 @@ size_t mw_chunk_attn_cached_workspace_size(const mw_kvcache* c, int n_queued, in
  * query tiles of each head, of which the *n_whole heaviest (the last) run
  * unsplit; *n_splits = 1 means no split and then *n_whole = 0.  The plan comes
  * from a cost model of the kernel's dispatch and does not change the result
- * beyond fp32 rounding.  Host-only: no device work.
+ * beyond the rounding of fp32 sums and of the probabilities.  Host-only: no
+ * device work.
  * Errors: MW_EINVAL (null pointers, n_queued/q_len < 1, window < -1 or above
  * the live chunks, unknown flags), MW_EUNSUPPORTED (as mw_chunk_attn_cached). */
 int mw_chunk_attn_cached_plan(const mw_kvcache* c, int n_queued, int q_len, int window, int flags,

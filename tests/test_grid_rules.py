@@ -41,14 +41,18 @@ def test_residency_on_the_device(mw, D, Tq, bm, bk, wgs):
     check_choice(D, Tq, bm, bk, wgs)
 
 
-def rule(symbol):
-    fn = mw.load()[symbol]
-    fn.restype, fn.argtypes = ctypes.c_int, [ctypes.c_int] * 3
-    return fn
+def rule(symbol, *args):
+    fn = mw.load()[symbol]  # loaded in the tests only: on a GPU, torch comes first
+    fn.restype, fn.argtypes = ctypes.c_int, [ctypes.c_int] * len(args)
+    return fn(*args)
 
 
-fwd_fill = rule("_ZN2mw17training_fwd_fillEiii")  # mw::training_fwd_fill(int, int, int)
-bwd_grid = rule("_ZN2mw17training_bwd_gridEiii")  # mw::training_bwd_grid(int, int, int)
+def fwd_fill(D, BH, T):
+    return rule("_ZN2mw17training_fwd_fillEiii", D, BH, T)  # mw::training_fwd_fill(int, int, int)
+
+
+def bwd_grid(D, BH, T):
+    return rule("_ZN2mw17training_bwd_gridEiii", D, BH, T)  # mw::training_bwd_grid(int, int, int)
 
 
 @pytest.mark.parametrize("D,BH,T,fill", [
