@@ -132,9 +132,13 @@ FwdChoice fwd_choice_decode_128(int Tq);
 //           12 x 1500 (45 | - | 26 | 27); D = 64, 4 x 4000 (86 | 61 | 40 | 28).  A
 //           short sequence does not repay merging four groups: D = 128,
 //           8 x 600 (25 | - | 12 | 14); D = 64, 2 x 256 (13 | 7.5 | 5.4 | 5.9).
-//   small   up to 1.5 rounds of resident 64-row workgroups: D = 128, 24 x 2000
-//           (56 | 47 | 47); D = 72, 16 x 3000 (67 | 53 | 43), 24 x 3600 (94 | 90 | 90);
-//           D = 64, 24 x 3600 (89 | 76 | 69).
+//   small   up to 1.5 rounds of resident 64-row workgroups, at D = 72 and 128 about
+//           one where the sequence is short and its tiles of much the same weight:
+//           D = 128, 24 x 2000 (56 | 47 | 47), against 128 rows 12 x 2800 +15%, 9 x
+//           4800 +9%, 24 x 1500 +14%, 36 x 1000 +7%, 64 x 512 +14%, 40 x 1000 -4%, 96 x
+//           330 -10%, 144 x 200 -13%; D = 72, 16 x 3000 (67 | 53 | 43), 24 x 3600
+//           (94 | 90 | 90), 25 x 3000 +4%, 56 x 1000 +8%, 64 x 1000 -7%, 96 x 512 +5%, 112 x
+//           512 -19%; D = 64, 24 x 3600 (89 | 76 | 69), 40 x 2048 +2%, 128 x 512 +8%.
 //   mid     D = 128 up to 1.5 rounds of resident 128-row workgroups: 16 x 4800
 //           (131 | 118 | 130), 12 x 7200 (198 | 179 | 208), 12 x 9600 (300 | 314 | -).
 //   large   D = 64 from about two rounds of 256-row workgroups on, whose two row
@@ -147,7 +151,10 @@ inline GridFill grid_fill(int D, int BH, int Tk) {
   const long long tiles = (long long)BH * ((Tk + 63) / 64);
   if (tiles <= 256 && Tk >= (D == 128 ? 1536 : 512)) return GridFill::sparse;
   if (tiles <= (D == 64 ? 512 : 384) && Tk >= 2048) return GridFill::sparse;
-  if (tiles <= (D == 128 ? 768 : (D == 72 ? 1152 : 1536))) return GridFill::small;
+  const int small = D == 64    ? 1536
+                    : D == 72 ? (Tk < 768 ? 800 : Tk < 2500 ? 960 : 1152)
+                              : (Tk < 256 ? 384 : Tk < 1000 ? 544 : Tk < 2048 ? 608 : 768);
+  if (tiles <= small) return GridFill::small;
   if (D == 128 && tiles <= 1536) return GridFill::mid;
   return D == 64 && tiles > 4300 ? GridFill::large : GridFill::full;
 }

@@ -28,7 +28,7 @@ HISTORY = [
     (72, 1, 2, 33, 1, 20, GROUPS4), (72, 1, 2, 33, 1, 5, PLAN), (72, 15, 20, 60, 1, 3, ROWS128),
     (72, 1, 2, 100, 2, 6, GROUPS4), (72, 1, 3, 90, 2, 2, GROUPS2), (72, 3, 20, 110, 2, 4, GROUPS2),
     (72, 8, 16, 100, 2, 4, PLAN), (128, 1, 2, 200, 3, 6, GROUPS4), (128, 1, 2, 192, 3, 4, GROUPS2),
-    (128, 3, 14, 192, 3, 2, GROUPS2), (128, 4, 15, 192, 3, 2, PLAN), (128, 7, 16, 192, 3, 2, PLAN)]
+    (128, 3, 12, 192, 3, 2, GROUPS2), (128, 4, 15, 192, 3, 2, PLAN), (128, 7, 16, 192, 3, 2, PLAN)]
 
 
 @pytest.mark.parametrize("D,B,H,L,nq,n_hist,tile", HISTORY)

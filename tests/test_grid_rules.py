@@ -58,7 +58,8 @@ def bwd_grid(D, BH, T):
 @pytest.mark.parametrize("D,BH,T,fill", [
     (64, 16, 42240, LARGE), (64, 16, 19200, LARGE), (64, 7, 42240, LARGE), (64, 96, 4800, LARGE),
     (64, 24, 10560, FULL), (64, 8, 19200, FULL), (64, 4, 42240, FULL), (72, 16, 19200, FULL), (128, 16, 42240, FULL),
-    (128, 16, 4800, MID), (72, 16, 3000, SMALL), (64, 4, 4000, SPARSE)])
+    (128, 16, 4800, MID), (72, 16, 3000, SMALL), (128, 144, 200, MID), (128, 96, 330, MID), (128, 64, 512, SMALL),
+    (128, 36, 1000, SMALL), (128, 12, 2800, SMALL), (72, 112, 512, FULL), (72, 64, 1000, FULL), (72, 56, 1000, SMALL), (64, 4, 4000, SPARSE)])
 def test_forward_lines(D, BH, T, fill):
     assert fwd_fill(D, BH, T) == fill
 
