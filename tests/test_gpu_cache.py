@@ -59,8 +59,9 @@ def test_cached_attention_vs_oracle(mw, split, mode, B, H, D, L, S, n_commit, wi
 
 
 def test_cached_full_history_equals_training_rows(mw):
-    """A window holding all committed history gives the training forward's rows (bit-exact:
-    both visit the same keys in the same order)."""
+    """A window holding all committed history gives the training forward's rows, bit-exact at D = 128
+    for more than 512 queued rows in an unsplit call: both then visit the same keys in the same order
+    and wave groups.  (test_gpu_unsplit_tiles has the other head widths, sizes and tiles.)"""
     import torch
     B, H, D, L, nq = 1, 2, 128, 192, 3
     hist = make_chunks(4, B, H, L, D, seed=500)
