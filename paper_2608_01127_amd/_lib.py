@@ -197,13 +197,13 @@ def _plain_views(ts, shape, ref) -> bool:
     """Whether every tensor is a bf16 [B,H,T,D] view of `shape` on the GPU of `ref` with a contiguous
     last dimension: what the checks below find one by one, in a sixth of their time.  A call
     whose tensors are not goes through them, for their errors."""
-    torch = _torch()
-    if not isinstance(ref, torch.Tensor) or len(shape) != 4:
+    try:
+        index = ref.get_device()
+    except AttributeError:  # no tensor
         return False
-    index = ref.get_device()
-    if index < 0:
+    if index < 0 or len(shape) != 4:
         return False
-    bf16 = torch.bfloat16
+    bf16 = _torch().bfloat16
     for t in ts:
         if t.dtype is not bf16 or t.shape != shape or t.get_device() != index or t.stride()[-1] != 1:
             return False
