@@ -414,11 +414,11 @@ __device__ __forceinline__ int xcd_remap(int bid, int n) {
 // stream every head's K/V: forward, D = 72, [B, T, H, D] views, 45 heads x 19200
 // 5502 -> 3642 us (one after another 4340), 99 x 3000 329 -> 205 (306).
 __host__ __device__ __forceinline__ void tile_item(int bid, int BH, int& bh, int& rank) {
-  rank = bid / BH;
-  const int p = bid - rank * BH, lead = BH % 8;
-  const int first = p < lead ? 0 : lead, n = p < lead ? lead : BH - lead;
-  const int low = n & -n, g = low < 8 ? low : 8;  // 1, 2, 4 or 8
-  bh = first + (bid & (g - 1)) * (n / g) + (p - first) / g;
+  const unsigned u = bid, heads = BH, r = u / heads, p = u - r * heads, lead = heads % 8;
+  const unsigned first = p < lead ? 0 : lead, n = p < lead ? lead : heads - lead;
+  const unsigned low = n & -n, g = low < 8 ? low : 8;  // 1, 2, 4 or 8
+  rank = r;
+  bh = first + (u & (g - 1)) * (n / g) + (p - first) / g;
 }
 
 // Cached attention: the heads one after another on each XCD (xcd_remap).
